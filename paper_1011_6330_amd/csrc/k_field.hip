@@ -7,7 +7,6 @@
 // bit-identical to an IEEE double evaluation of the same formulas.
 #include <math.h>
 
-#include "diag_body.h"
 #include "pcpic_internal.h"
 #include "short_math.h"
 #include "wave.h"
@@ -26,31 +25,7 @@ __global__ __launch_bounds__(256) void k_rho_gj(Consts c, const double *knots, d
         rho[i] = r;
         a = fabs(r);
     }
-    // max |rho_GJ| for the Gauss normalisation (non-negative doubles order as integers)
-    long long m = wave_max_i64(__builtin_bit_cast(long long, a));
-    if (__lane_id() == 0) atomicMax(&ctr->rho_max_bits, (unsigned long long)m);
-}
-
-// CIC node weights of the live particles (node weight W_i = S_i - S_{i-1}).
-__global__ __launch_bounds__(256) void k_weights(Consts c, const double *__restrict__ X,
-                                                 const DevCounters *ctr, unsigned long long *w)
-{
-    int64_t lo, hi;
-    block_range(ctr->n_slots, gridDim.x, blockIdx.x, lo, hi);
-    WeightAcc acc;
-    for (int64_t base = lo; base < hi; base += 256) {
-        const int64_t p = base + threadIdx.x;
-        const double x = p < hi ? X[p] : -1.0;
-        const bool live = x >= 0.0 && x < (double)c.N;
-        int64_t cell = 0, F = 0;
-        if (live) {
-            const double cd = floor(x);
-            cell = (int64_t)cd;
-            F = (int64_t)rint((x - cd) * c.twoP);
-        }
-        acc.add(w, live, cell, c.oneP, F);
-    }
-    acc.flush(w);
+    block_max_abs(&ctr->rho_max_bits, a);   // max |rho_GJ| for the Gauss normalisation
 }
 
 // Right-hand side of eq. (4) times dz^2 on nodes 1..N; node N carries the
@@ -478,23 +453,12 @@ hipError_t launch_rho_gj(pic_handle *h)
     return hipGetLastError();
 }
 
-hipError_t launch_weights(pic_handle *h, int64_t *w_out)
-{
-    const Consts &c = h->c;
-    hipLaunchKernelGGL(k_fill_i64, dim3(grid_for(c.N + 1, 256)), dim3(256), 0, h->stream, w_out,
-                       c.N + 1, (int64_t)0);
-    if (h->p.precision == PIC_FP32_BULK) return launch_weights32(h, w_out);
-    hipLaunchKernelGGL(k_weights, dim3(h->n_cu * 8), dim3(256), 0, h->stream, c, h->ws.x[h->pbuf],
-                       h->ws.ctr, (unsigned long long *)w_out);
-    return hipGetLastError();
-}
-
 // Right-hand side of eq. (4) from the loaded charge (before the solve).
 hipError_t launch_poisson_rhs(pic_handle *h)
 {
     const Consts &c = h->c;
     Workspace &w = h->ws;
-    hipError_t e = launch_weights(h, w.w);
+    hipError_t e = launch_moments(h, 0, ProfPtrs{}, w.w, false);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_poisson_rhs, dim3(grid_for(c.N, 256)), dim3(256), 0, h->stream, c, w.w,
                        w.rho_gj, w.rhs);

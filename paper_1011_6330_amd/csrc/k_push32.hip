@@ -20,7 +20,6 @@
 #include "push_common.h"
 #include "push_body.h"
 #include "sort_body.h"
-#include "diag_body.h"
 
 namespace pcpic {
 
@@ -31,78 +30,8 @@ __global__ __launch_bounds__(BLOCK) void k_push_f32(Consts c, Push32Args a)
 }
 
 // ------------------------------------------------------------------------
-// diagnostics, sort and append for the two streams
+// sort and append for the two streams
 // ------------------------------------------------------------------------
-
-// Block b's contiguous range of the slots of both streams taken end to end
-// (the low stream's, then the high stream's): [lo0, hi0) of the low stream and
-// [lo1, hi1) of the high stream, either possibly empty.
-__device__ __forceinline__ void stream_ranges(const DevCounters *ctr, int64_t &lo0, int64_t &hi0, int64_t &lo1,
-                                              int64_t &hi1)
-{
-    const int64_t n_lo = ctr->n_slots, n_hi = ctr->n_slots_hi;
-    int64_t a, b;
-    block_range(n_lo + n_hi, gridDim.x, blockIdx.x, a, b);
-    lo0 = a < n_lo ? a : n_lo;
-    hi0 = b < n_lo ? b : n_lo;
-    lo1 = (a > n_lo ? a : n_lo) - n_lo;
-    hi1 = (b > n_lo ? b : n_lo) - n_lo;
-}
-
-__global__ __launch_bounds__(256) void k_weights32(Consts c, Streams s, const DevCounters *ctr,
-                                                   unsigned long long *w)
-{
-    int64_t r[4];
-    stream_ranges(ctr, r[0], r[1], r[2], r[3]);
-    WeightAcc acc;
-#pragma unroll 1
-    for (int high = 0; high < 2; ++high) {
-        const int64_t hi = r[2 * high + 1];
-        for (int64_t base = r[2 * high]; base < hi; base += 256) {
-            const int64_t p = base + threadIdx.x;
-            float off = 0.0f;
-            int cell = -1;
-            if (p < hi) {
-                if (high) cell = hi_slot(s, p, off);
-                else { cell = s.CL[p]; off = s.OL[p]; }
-            }
-            const bool live = cell >= 0;
-            int64_t F = 0;
-            if (live) F = (int64_t)rint((double)off * c.twoP);
-            acc.add(w, live, cell, c.oneP, F);
-        }
-    }
-    acc.flush(w);
-}
-
-__global__ __launch_bounds__(256) void k_profile32(Consts c, int nb, Streams s, const DevCounters *ctr, ProfOut o)
-{
-    int64_t r[4];
-    stream_ranges(ctr, r[0], r[1], r[2], r[3]);
-    ProfAcc acc;
-#pragma unroll 1
-    for (int high = 0; high < 2; ++high) {
-        const int64_t hi = r[2 * high + 1];
-        for (int64_t base = r[2 * high]; base < hi; base += 256) {
-            const int64_t p = base + threadIdx.x;
-            float off = 0.0f;
-            int cell = -1;
-            if (p < hi) {
-                if (high) cell = hi_slot(s, p, off);
-                else { cell = s.CL[p]; off = s.OL[p]; }
-            }
-            const bool want = cell >= 0;
-            int64_t bin = 0, gi = 0, gf = 0;
-            long long ob = 0;
-            if (want) {
-                const double u = high ? s.UH[p] : (double)s.UL[p];
-                prof_values(c, nb, (double)cell + (double)off, u, bin, gi, gf, ob);
-            }
-            acc.add(o, want, bin, gi, gf, ob);
-        }
-    }
-    acc.flush(o);
-}
 
 // Histogram for the sort (sort_key_f32: the destination stream's key range),
 // one block per tile of either stream (sort_item).
@@ -300,21 +229,6 @@ hipError_t launch_push_f32(pic_handle *h)
         if (B == 512) return launch_push32_t<512, 0>(h);
     }
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_weights32(pic_handle *h, int64_t *w_out)
-{
-    hipLaunchKernelGGL(k_weights32, dim3(h->n_cu * 8), dim3(256), 0, h->stream, h->c, streams_of(h, h->pbuf),
-                       h->ws.ctr, (unsigned long long *)w_out);
-    return hipGetLastError();
-}
-
-hipError_t launch_profile32(pic_handle *h, int nbins, const ProfPtrs &p)
-{
-    const Workspace &w = h->ws;
-    hipLaunchKernelGGL(k_profile32, dim3(h->n_cu * 8), dim3(256), 0, h->stream, h->c, nbins, streams_of(h, h->pbuf),
-                       w.ctr, ProfOut{p.cnt, p.lo, p.hi, p.mn, p.mx});
-    return hipGetLastError();
 }
 
 // Blocks of a pass over both streams in tiles of SORT_TILE slots (sort_item).

@@ -346,7 +346,6 @@ namespace pcpic {
 
 // ---- kernel launchers (each enqueues on h->stream, returns hipError_t) ----
 hipError_t launch_rho_gj(pic_handle *h);
-hipError_t launch_weights(pic_handle *h, int64_t *w_out);
 hipError_t launch_poisson(pic_handle *h);
 hipError_t launch_poisson_rhs(pic_handle *h);
 hipError_t launch_fields_from_phi(pic_handle *h);
@@ -357,7 +356,6 @@ hipError_t launch_push_f64_ptrs(pic_handle *h, const double *X, const double *U,
                                 const double *ez);
 hipError_t launch_field_ptrs(pic_handle *h, const double *ezo, const double *ero, const double *bo, double *ezn,
                              double *ern, double *bn, double *X, double *U);
-hipError_t launch_weights32(pic_handle *h, int64_t *w_out);
 // Profile bins: count, 128-bit sum (low and high words), ordered bit images of min and max.
 struct ProfPtrs {
     long long *cnt;
@@ -365,10 +363,10 @@ struct ProfPtrs {
     long long *hi;
     long long *mn, *mx;
 };
-hipError_t launch_profile32(pic_handle *h, int nbins, const ProfPtrs &p);
-// The profile accumulated into the bins p (cleared first; clear_gauss also clears the
-// Gauss maximum of the diagnostics), and copied out in the caller's layout.
-hipError_t launch_profile_into(pic_handle *h, int nb, const ProfPtrs &p, bool clear_gauss);
+// The profile accumulated into the bins p (nb > 0) and the node weights into w_out
+// (non-null), both cleared first; clear_gauss also clears the Gauss maximum.
+hipError_t launch_moments(pic_handle *h, int nb, const ProfPtrs &p, int64_t *w_out, bool clear_gauss);
+// The bins copied out in the caller's layout.
 hipError_t launch_profile_finish(pic_handle *h, int nb, const ProfPtrs &p, int64_t *count, uint64_t *sum_lo,
                                  int64_t *sum_hi, double *vmin, double *vmax);
 hipError_t launch_sort32_hist(pic_handle *h);
@@ -392,7 +390,6 @@ hipError_t launch_check_append(pic_handle *h, int64_t base, int64_t n);
 hipError_t launch_commit_append(pic_handle *h, int64_t n);
 hipError_t launch_kick(pic_handle *h);
 hipError_t launch_gauss(pic_handle *h);
-hipError_t launch_profile(pic_handle *h, int n_bins);
 // Counting sort; hist_ready = the key counts were accumulated by the step before.
 hipError_t launch_sort(pic_handle *h, bool hist_ready);
 hipError_t launch_clear_hist(pic_handle *h);

@@ -757,9 +757,10 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
     if (req && !(req->gauss_tol >= 0.0)) return fail(PIC_EINVAL, "gauss_tol must be >= 0");
     const int64_t N = h->c.N;
     const Workspace &w = h->ws;
-    HIP_OK(launch_profile(h, nb));   // also clears the Gauss maximum
-    if (want_gauss || out->gauss) HIP_OK(launch_gauss(h));
-    else if (out->weights) HIP_OK(launch_weights(h, w.w));
+    const bool gauss = want_gauss || out->gauss;
+    HIP_OK(launch_moments(h, nb, ProfPtrs{w.pcount, w.plo, w.phi128, w.pmin, w.pmax},
+                          gauss || out->weights ? w.w : nullptr, true));
+    if (gauss) HIP_OK(launch_gauss(h));
     DevCounters ctr;
     HIP_OK(hipMemcpyAsync(&ctr, w.ctr, sizeof ctr, hipMemcpyDeviceToHost, h->stream));
     const int f = h->fbuf;
@@ -857,7 +858,7 @@ pic_status pic_profile_noalloc(pic_handle *h, int32_t n_bins, int64_t *d_count, 
     long long *p = (long long *)base;
     const size_t nb = (size_t)n_bins;
     const ProfPtrs bins{p, (unsigned long long *)(p + nb), p + 2 * nb, p + 3 * nb, p + 4 * nb};
-    HIP_OK(launch_profile_into(h, n_bins, bins, false));
+    HIP_OK(launch_moments(h, n_bins, bins, nullptr, false));
     HIP_OK(launch_profile_finish(h, n_bins, bins, d_count, d_sum_lo, d_sum_hi, d_min, d_max));
     return PIC_OK;
 }

@@ -13,16 +13,6 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v)
     return v;
 }
 
-__device__ __forceinline__ long long wave_min_i64(long long v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        long long o = __shfl_xor(v, off);
-        v = o < v ? o : v;
-    }
-    return v;
-}
-
 __device__ __forceinline__ long long wave_max_i64(long long v)
 {
 #pragma unroll
@@ -59,26 +49,6 @@ __device__ __forceinline__ WaveRun wave_runs(long long key, bool want)
     r.rank = lane - r.head;
     r.end = brk ? __ffsll(brk) - 1 : 64;
     return r;
-}
-
-// Add `val` to dst[key] for every lane with `want`, one global atomic per
-// distinct key present in the wave: lanes sharing the leader's key are summed
-// with a butterfly, the leader lane issues the atomic, and the loop repeats
-// over the keys still pending.  Integer addition makes the result independent
-// of the order in which waves and lanes arrive.
-__device__ __forceinline__ void wave_add_keyed(unsigned long long *dst, int64_t key, int64_t val,
-                                               bool want)
-{
-    unsigned long long pend = __ballot(want);
-    while (pend) {
-        const int leader = __ffsll((unsigned long long)pend) - 1;
-        const int64_t lk = __shfl(key, leader);
-        const bool mine = want && key == lk;
-        const int64_t v = wave_sum_i64(mine ? val : 0);
-        if ((int)__lane_id() == leader && v != 0) atomicAdd(dst + lk, (unsigned long long)v);
-        pend &= ~__ballot(mine);
-        want = want && !mine;
-    }
 }
 
 // 128-bit two's-complement accumulation into (lo, hi) words with carry.
@@ -190,6 +160,25 @@ __device__ __forceinline__ double wave_max_f64_to63(double v)
     v = fmax(v, dpp_f64<0x142, 0xa>(v));
     v = fmax(v, dpp_f64<0x143, 0xc>(v));
     return v;
+}
+
+// Block maximum of |a| (256 threads) into *dst, as bit images (they order as the
+// magnitudes do, a NaN above infinity): one atomic per block, and none when the
+// word already holds as much (it only grows, so a stale read costs at most a
+// redundant atomic).  With one
+// atomic per wave, the 1,024 waves of a 65,536-cell tube took 15 us on it.
+// Every thread of the block must call it.
+__device__ __forceinline__ void block_max_abs(unsigned long long *dst, double a)
+{
+    __shared__ unsigned long long s_m[4];
+    const long long m = wave_max_i64(__builtin_bit_cast(long long, fabs(a)));
+    if (__lane_id() == 0) s_m[threadIdx.x >> 6] = (unsigned long long)m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long v = s_m[0];
+        for (int k = 1; k < 4; ++k) v = s_m[k] > v ? s_m[k] : v;
+        if (v != 0 && v > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, v);
+    }
 }
 
 // Minimum (maximum) of an int32 over the 64 lanes, returned in every lane: the
