@@ -329,24 +329,24 @@ class Tube(_TubeOps):
         d = PicDiag()
         out = {}
         if fields:
-            out["ez"], out["er"], out["b_phi"] = np.zeros(N), np.zeros(N + 1), np.zeros(N)
+            out["ez"], out["er"], out["b_phi"] = np.empty(N), np.empty(N + 1), np.empty(N)
             d.ez, d.er, d.b_phi = _ptr(out["ez"]), _ptr(out["er"]), _ptr(out["b_phi"])
         if rho:
-            out["rho_gj"] = np.zeros(N + 1)
+            out["rho_gj"] = np.empty(N + 1)
             d.rho_gj = _ptr(out["rho_gj"])
         if j:
-            out["j_last"] = np.zeros(N, np.int64)
+            out["j_last"] = np.empty(N, np.int64)
             d.j_last = _ptr(out["j_last"], _pi)
         if weights:
-            out["weights"] = np.zeros(N + 1, np.int64)
+            out["weights"] = np.empty(N + 1, np.int64)
             d.weights = _ptr(out["weights"], _pi)
         if gauss:
-            out["gauss"] = np.zeros(N + 1)
+            out["gauss"] = np.empty(N + 1)
             d.gauss = _ptr(out["gauss"])
         if n_bins:
             for k, dt in (("prof_count", np.int64), ("prof_mean", np.float64), ("prof_min", np.float64),
                           ("prof_max", np.float64), ("prof_sum_lo", np.uint64), ("prof_sum_hi", np.int64)):
-                out[k] = np.zeros(n_bins, dt)
+                out[k] = np.empty(n_bins, dt)
             d.prof_count, d.prof_mean = _ptr(out["prof_count"], _pi), _ptr(out["prof_mean"])
             d.prof_min, d.prof_max = _ptr(out["prof_min"]), _ptr(out["prof_max"])
             d.prof_sum_lo, d.prof_sum_hi = _ptr(out["prof_sum_lo"], _pu), _ptr(out["prof_sum_hi"], _pi)

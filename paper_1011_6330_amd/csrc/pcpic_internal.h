@@ -8,6 +8,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -281,6 +282,14 @@ Workspace carve(const pic_params &p, uint8_t *base);
 // nominal density (ppc per cell), at most 16 bins.
 int sort_sub_log2(const pic_params &p);
 
+// Counts the live handles (the page-locked staging buffers go with the last one).
+struct HandleCount {
+    HandleCount();
+    ~HandleCount();
+    HandleCount(const HandleCount &) = delete;
+    HandleCount &operator=(const HandleCount &) = delete;
+};
+
 }  // namespace pcpic
 
 // The recorded forward of an adjoint run (pic_adjoint_forward), which
@@ -299,6 +308,7 @@ struct AdjRecord {
 };
 
 struct pic_handle {
+    pcpic::HandleCount count;
     pic_params p{};
     std::vector<double> knots;
     pcpic::Consts c{};
@@ -322,6 +332,7 @@ struct pic_handle {
     int dev = 0;        // device ordinal current at pic_init
     int64_t mut = 0;    // changes of the tube's state other than steps (inject, load, field or schedule writes)
     AdjRecord adj;      // the last recorded adjoint forward
+    std::atomic<int64_t> reads{0};   // diagnostics calls (a batch: of all its tubes)
     // batch (ensemble) handles
     bool is_batch = false;
     pic_handle *parent = nullptr;               // set on the tubes of a batch
@@ -369,6 +380,16 @@ hipError_t launch_moments(pic_handle *h, int nb, const ProfPtrs &p, int64_t *w_o
 // The bins copied out in the caller's layout.
 hipError_t launch_profile_finish(pic_handle *h, int nb, const ProfPtrs &p, int64_t *count, uint64_t *sum_lo,
                                  int64_t *sum_hi, double *vmin, double *vmax);
+// Gather of several device arrays (16-byte aligned) into one host-visible buffer.
+struct PackSeg {
+    const unsigned long long *src;
+    int64_t at, words;      // destination (even) and length in 8-byte words
+};
+struct PackArgs {
+    PackSeg seg[13];
+    int n;
+};
+hipError_t launch_pack(pic_handle *h, const PackArgs &a, void *dst);
 hipError_t launch_sort32_hist(pic_handle *h);
 hipError_t launch_sort32_scatter(pic_handle *h);
 hipError_t launch_append_staged(pic_handle *h, int64_t n, bool check_only);

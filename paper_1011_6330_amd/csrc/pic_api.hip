@@ -74,6 +74,109 @@ pic_status scratch_of_current_device(int *dev_out, void **out)
     return PIC_OK;
 }
 
+// ---- page-locked staging of the read-outs ----------------------------------
+//
+// A read-out takes a buffer for the duration of its call (it waits for the GPU
+// before it returns), so calls on several threads and streams each hold their
+// own, allocated by a handle's second read-out.  At most PINNED_KEEP idle buffers of at most PINNED_MAX bytes are kept,
+// and none once the last handle is gone.  Allocation runs in the relaxed capture
+// mode, so it never disturbs another thread's stream capture; where it fails the
+// caller copies into its own pageable memory instead.
+constexpr size_t PINNED_MIN = 64 << 10, PINNED_MAX = 4 << 20;
+constexpr size_t PINNED_KEEP = 8;
+
+class PinnedPool {
+public:
+    struct Block {
+        void *p;
+        size_t n;
+    };
+    void add_handle()
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        ++handles_;
+    }
+    void drop_handle()
+    {
+        Block gone[PINNED_KEEP];
+        size_t n = 0;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (--handles_ == 0) {
+                for (; n < n_idle_; ++n) gone[n] = idle_[n];
+                n_idle_ = 0;
+            }
+        }
+        for (size_t k = 0; k < n; ++k) (void)hipHostFree(gone[k].p);
+    }
+    // An idle buffer of at least n bytes, else (with `fresh`) a new one, else none.
+    Block take(size_t n, bool fresh)
+    {
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            size_t best = n_idle_;
+            for (size_t k = 0; k < n_idle_; ++k)
+                if (idle_[k].n >= n && (best == n_idle_ || idle_[k].n < idle_[best].n)) best = k;
+            if (best < n_idle_) {
+                const Block b = idle_[best];
+                idle_[best] = idle_[--n_idle_];
+                return b;
+            }
+        }
+        if (!fresh) return Block{nullptr, 0};
+        size_t sz = PINNED_MIN;
+        while (sz < n) sz *= 2;
+        void *p = nullptr;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (hipHostMalloc(&p, sz, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        return Block{p, p ? sz : 0};
+    }
+    void give(const Block &b)
+    {
+        if (!b.p) return;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (handles_ > 0 && n_idle_ < PINNED_KEEP) {
+                idle_[n_idle_++] = b;
+                return;
+            }
+        }
+        (void)hipHostFree(b.p);
+    }
+
+private:
+    std::mutex mu_;
+    Block idle_[PINNED_KEEP] = {};
+    size_t n_idle_ = 0;
+    int64_t handles_ = 0;
+};
+PinnedPool &g_pinned = *new PinnedPool();   // never destroyed: handles may outlive static destructors
+
+// A staging buffer held for the duration of a call.  It is given back only once
+// the stream's work on it is done (every user waits for the stream; an error path
+// waits here).
+struct Pinned {
+    PinnedPool::Block b;
+    hipStream_t stream;
+    bool idle = true;       // no GPU work on the buffer is pending
+    Pinned(size_t n, hipStream_t s, bool fresh)
+        : b(n <= PINNED_MAX ? g_pinned.take(n, fresh) : PinnedPool::Block{nullptr, 0}), stream(s)
+    {
+    }
+    ~Pinned()
+    {
+        if (!idle) (void)hipStreamSynchronize(stream);
+        g_pinned.give(b);
+    }
+    Pinned(const Pinned &) = delete;
+    Pinned &operator=(const Pinned &) = delete;
+};
+
 pic_status validate(const pic_params *p)
 {
     if (!p) return fail(PIC_EINVAL, "params is NULL");
@@ -170,6 +273,9 @@ Consts make_consts(const pic_params &p, const double *knots)
 }  // namespace
 
 namespace pcpic {
+
+HandleCount::HandleCount() { g_pinned.add_handle(); }
+HandleCount::~HandleCount() { g_pinned.drop_handle(); }
 
 int sort_sub_log2(const pic_params &p)
 {
@@ -309,8 +415,13 @@ pic_status write_high_stream(pic_handle *h, int b, int64_t ns, const int *cell, 
 
 pic_status read_counters(pic_handle *h, DevCounters *out)
 {
-    HIP_OK(hipMemcpyAsync(out, h->ws.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, h->stream));
+    Pinned st(sizeof(DevCounters), h->stream, false);
+    void *dst = st.b.p ? st.b.p : out;
+    st.idle = false;
+    HIP_OK(hipMemcpyAsync(dst, h->ws.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, h->stream));
     HIP_OK(hipStreamSynchronize(h->stream));
+    st.idle = true;
+    if (st.b.p) memcpy(out, dst, sizeof(DevCounters));
     return PIC_OK;
 }
 
@@ -318,6 +429,21 @@ double i128_to_double(unsigned long long lo, long long hi)
 {
     const __int128 v = ((__int128)hi << 64) | (__int128)lo;
     return (double)v;
+}
+
+// Every particle finite and inside [0, N); without branches, so that the loop is
+// vectorised (a test and a branch per particle took 0.7 ms for 1e6).
+bool host_particles_ok(const double *x, const double *u, int64_t n, double N)
+{
+    constexpr int64_t BLK = 4096;
+    for (int64_t b = 0; b < n; b += BLK) {
+        const int64_t e = b + BLK < n ? b + BLK : n;
+        int64_t bad = 0;
+        for (int64_t i = b; i < e; ++i)
+            bad |= (int64_t)!(x[i] >= 0.0) | (int64_t)!(x[i] < N) | (int64_t)!(fabs(u[i]) <= 1.7976931348623157e308);
+        if (bad) return false;
+    }
+    return true;
 }
 
 }  // namespace
@@ -420,7 +546,7 @@ pic_status pic_inject(pic_handle *h, int64_t n, const double *x, const double *u
         return fail(PIC_EINVAL, "bad arguments to pic_inject");
     if (n == 0) return PIC_OK;
     h->mut += 1;
-    if (mem == 0) {
+    if (mem == 0 && !host_particles_ok(x, u, n, (double)h->c.N)) {
         for (int64_t i = 0; i < n; ++i) {
             if (!isfinite(u[i]) || !isfinite(x[i])) return fail(PIC_ENONFINITE, "particle %lld not finite", (long long)i);
             if (!(x[i] >= 0.0 && x[i] < (double)h->c.N))
@@ -758,38 +884,71 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
     const int64_t N = h->c.N;
     const Workspace &w = h->ws;
     const bool gauss = want_gauss || out->gauss;
-    HIP_OK(launch_moments(h, nb, ProfPtrs{w.pcount, w.plo, w.phi128, w.pmin, w.pmax},
-                          gauss || out->weights ? w.w : nullptr, true));
+    if (nb > 0 || gauss || out->weights)
+        HIP_OK(launch_moments(h, nb, ProfPtrs{w.pcount, w.plo, w.phi128, w.pmin, w.pmax},
+                              gauss || out->weights ? w.w : nullptr, gauss));
     if (gauss) HIP_OK(launch_gauss(h));
-    DevCounters ctr;
-    HIP_OK(hipMemcpyAsync(&ctr, w.ctr, sizeof ctr, hipMemcpyDeviceToHost, h->stream));
     const int f = h->fbuf;
-    if (out->ez) HIP_OK(hipMemcpyAsync(out->ez, w.ez[f], (size_t)N * 8, hipMemcpyDeviceToHost, h->stream));
-    if (out->er) HIP_OK(hipMemcpyAsync(out->er, w.er[f], (size_t)(N + 1) * 8, hipMemcpyDeviceToHost, h->stream));
-    if (out->b_phi) HIP_OK(hipMemcpyAsync(out->b_phi, w.b[f], (size_t)N * 8, hipMemcpyDeviceToHost, h->stream));
-    if (out->rho_gj) HIP_OK(hipMemcpyAsync(out->rho_gj, w.rho_gj, (size_t)(N + 1) * 8, hipMemcpyDeviceToHost, h->stream));
-    if (out->j_last)
-        HIP_OK(hipMemcpyAsync(out->j_last, w.j[1 - h->jbuf], (size_t)N * 8, hipMemcpyDeviceToHost, h->stream));
-    if (out->weights) HIP_OK(hipMemcpyAsync(out->weights, w.w, (size_t)(N + 1) * 8, hipMemcpyDeviceToHost, h->stream));
-    // The L2 norm of the residual is summed on the host in node order, so it
-    // does not depend on a device reduction order.
-    std::vector<double> gtmp;
+    std::vector<double> gtmp;                 // the residual, for its L2 norm, where the caller does not take it
     double *gdst = out->gauss;
     if (want_gauss && !gdst) {
         gtmp.resize((size_t)(N + 1));
         gdst = gtmp.data();
     }
-    if (gdst) HIP_OK(hipMemcpyAsync(gdst, w.gauss, (size_t)(N + 1) * 8, hipMemcpyDeviceToHost, h->stream));
-    std::vector<long long> cnt(nb), hi(nb), mn(nb), mx(nb);
-    std::vector<unsigned long long> lo(nb);
-    if (nb > 0) {
-        HIP_OK(hipMemcpyAsync(cnt.data(), w.pcount, (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
-        HIP_OK(hipMemcpyAsync(lo.data(), w.plo, (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
-        HIP_OK(hipMemcpyAsync(hi.data(), w.phi128, (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
-        HIP_OK(hipMemcpyAsync(mn.data(), w.pmin, (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
-        HIP_OK(hipMemcpyAsync(mx.data(), w.pmax, (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
+    DevCounters ctr;
+    std::vector<long long> prof((size_t)nb * 5);
+    long long *cnt = prof.data(), *hi = cnt + 2 * nb, *mn = cnt + 3 * nb, *mx = cnt + 4 * nb;
+    unsigned long long *lo = (unsigned long long *)(cnt + nb);
+    // what is read: gathered into one page-locked buffer by one kernel, as far as it
+    // fits; the rest (and everything, where no buffer is to be had) array by array
+    struct Want {
+        void *dst;
+        const void *src;
+        size_t bytes;
+    };
+    const size_t nbytes = (size_t)nb * 8;
+    const Want all[13] = {{&ctr, w.ctr, sizeof ctr},
+                          {cnt, w.pcount, nbytes},
+                          {lo, w.plo, nbytes},
+                          {hi, w.phi128, nbytes},
+                          {mn, w.pmin, nbytes},
+                          {mx, w.pmax, nbytes},
+                          {out->ez, w.ez[f], (size_t)N * 8},
+                          {out->er, w.er[f], (size_t)(N + 1) * 8},
+                          {out->b_phi, w.b[f], (size_t)N * 8},
+                          {out->rho_gj, w.rho_gj, (size_t)(N + 1) * 8},
+                          {out->j_last, w.j[1 - h->jbuf], (size_t)N * 8},
+                          {out->weights, w.w, (size_t)(N + 1) * 8},
+                          {gdst, w.gauss, (size_t)(N + 1) * 8}};
+    Want packed[13];
+    PackArgs pk{};
+    size_t total = 0;
+    for (const Want &a : all) {
+        if (!a.dst || a.bytes == 0) continue;
+        const size_t sz = (a.bytes + 15) & ~(size_t)15;
+        if (total + sz > PINNED_MAX) continue;
+        pk.seg[pk.n] = PackSeg{(const unsigned long long *)a.src, (int64_t)(total / 8), (int64_t)(a.bytes / 8)};
+        packed[pk.n++] = a;
+        total += sz;
+    }
+    // a handle's first read-out does not allocate: a buffer costs about 30 us to get
+    // and 120 us to give back, a tube that is read once would lose by it
+    Pinned st(total, h->stream, (h->parent ? h->parent : h)->reads.fetch_add(1) > 0);
+    st.idle = false;
+    if (st.b.p) HIP_OK(launch_pack(h, pk, st.b.p));
+    int at = 0;
+    for (const Want &a : all) {
+        if (!a.dst || a.bytes == 0) continue;
+        if (at < pk.n && packed[at].src == a.src) {
+            ++at;
+            if (st.b.p) continue;
+        }
+        HIP_OK(hipMemcpyAsync(a.dst, a.src, a.bytes, hipMemcpyDeviceToHost, h->stream));
     }
     HIP_OK(hipStreamSynchronize(h->stream));
+    st.idle = true;
+    if (st.b.p)
+        for (int k = 0; k < pk.n; ++k) memcpy(packed[k].dst, (char *)st.b.p + pk.seg[k].at * 8, packed[k].bytes);
     out->step = ctr.step;
     out->n_slots = ctr.n_slots + ctr.n_slots_hi;
     out->n_alive = ctr.n_slots + ctr.n_slots_hi - ctr.n_removed;
@@ -816,8 +975,13 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
     }
     out->gauss_l2 = 0.0;
     if (gdst && N > 1) {
-        double ss = 0.0;
-        for (int64_t i = 1; i < N; ++i) ss += gdst[i] * gdst[i];
+        // summed on the host in eight interleaved sums, in a fixed order
+        double q[8] = {};
+        int64_t i = 1;
+        for (; i + 8 <= N; i += 8)
+            for (int k = 0; k < 8; ++k) q[k] += gdst[i + k] * gdst[i + k];
+        for (; i < N; ++i) q[0] += gdst[i] * gdst[i];
+        const double ss = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
         out->gauss_l2 = sqrt(ss / (double)(N - 1)) / (h->c.fourpi * rmax);
     }
     for (int k = 0; k < nb; ++k) {

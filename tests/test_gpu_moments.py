@@ -61,3 +61,23 @@ def test_profile_and_weights_exact(precision, N, n, nb, load):
     only = t.diagnostics(n_bins=nb)
     assert np.array_equal(only["prof_sum_lo"], lo) and np.array_equal(t.diagnostics(weights=True)["weights"], w)
     t.close()
+
+
+# read-outs through the page-locked buffer (from a handle's second on) and array by array (its first, and what is
+# past the buffer's 4 MiB): the same values
+@pytest.mark.parametrize("N", [3, 1001, 120001, 600001])
+def test_repeated_readouts_equal_the_first(N):
+    from paper_1011_6330_amd import Tube
+    n = 5000
+    cfg = dict(synth.preset("c2"), n_cells=N, q_over_m=-1.0, ppc=max(n / N, 1e-3), capacity=n + 5000, sort_every=0, flags=1)
+    t = Tube(synth.tube_params(cfg))
+    t.inject(*synth.random_particles(N, n, seed=3))
+    ask = dict(n_bins=77, fields=True, gauss=True, j=True, weights=True, rho=True)
+    first, again = t.diagnostics(**ask), t.diagnostics(**ask)
+    other = Tube(synth.tube_params(cfg))
+    for d in (again, t.diagnostics(**ask)):
+        assert d.keys() == first.keys()
+        for k, v in first.items():
+            assert np.array_equal(d[k], v), k
+    other.close()
+    t.close()
