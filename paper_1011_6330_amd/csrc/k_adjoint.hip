@@ -17,6 +17,7 @@
 #include <math.h>
 
 #include "pcpic_internal.h"
+#include "thomas_body.h"
 #include "wave.h"
 
 namespace pcpic {
@@ -383,68 +384,10 @@ __global__ __launch_bounds__(256) void k_adj_phi(Consts c, const double *lez, co
 // Transposed Thomas solve A^T y = g (A: eq. (4) rows 1..N-1 = 1, bdiag, 1 and
 // row N = 2, bdiag; A^T carries the 2 on the super-diagonal of row N-1), then
 // dL/d rho_GJ,i = 4 pi dz^2 y_i (the right-hand side is -4 pi dz^2 (rho - rho_GJ)).
-constexpr int ADJ_CHUNK = 2048;
 __global__ __launch_bounds__(256) void k_adj_poisson(Consts c, const double *g, double *cp, double *dp,
                                                      double *g_rho)
 {
-    __shared__ double sa[ADJ_CHUNK];
-    __shared__ double sb[ADJ_CHUNK];
-    __shared__ double carry[2];
-    const int64_t N = c.N;
-    if (threadIdx.x == 0) { carry[0] = 0.0; carry[1] = 0.0; }
-    for (int64_t base = 1; base <= N; base += ADJ_CHUNK) {
-        const int cnt = (int)((N - base + 1) < ADJ_CHUNK ? (N - base + 1) : ADJ_CHUNK);
-        __syncthreads();
-        for (int t = threadIdx.x; t < cnt; t += 256) sa[t] = g[base + t];
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double pc = carry[0], pd = carry[1];
-            for (int t = 0; t < cnt; ++t) {
-                const int64_t i = base + t;
-                const double sup = (i <= N - 1) ? ((i == N - 1) ? 2.0 : 1.0) : 0.0;
-                double ci, di;
-                if (i == 1) {
-                    ci = sup / c.bdiag;
-                    di = sa[t] / c.bdiag;
-                } else {
-                    const double m = c.bdiag - pc;
-                    ci = sup / m;
-                    di = (sa[t] - pd) / m;
-                }
-                sa[t] = di;
-                sb[t] = ci;
-                pc = ci;
-                pd = di;
-            }
-            carry[0] = pc;
-            carry[1] = pd;
-        }
-        __syncthreads();
-        for (int t = threadIdx.x; t < cnt; t += 256) { dp[base + t] = sa[t]; cp[base + t] = sb[t]; }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) carry[0] = 0.0;
-    for (int64_t top = N; top >= 1; top -= ADJ_CHUNK) {
-        const int64_t lo = top - ADJ_CHUNK + 1 > 1 ? top - ADJ_CHUNK + 1 : 1;
-        const int cnt = (int)(top - lo + 1);
-        __syncthreads();
-        for (int t = threadIdx.x; t < cnt; t += 256) { sa[t] = dp[lo + t]; sb[t] = cp[lo + t]; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double next = carry[0];
-            for (int t = cnt - 1; t >= 0; --t) {
-                const int64_t i = lo + t;
-                const double v = (i == N) ? sa[t] : sa[t] - sb[t] * next;
-                sa[t] = v;
-                next = v;
-            }
-            carry[0] = next;
-        }
-        __syncthreads();
-        const double fac = c.fourpi * (c.dz * c.dz);
-        for (int t = threadIdx.x; t < cnt; t += 256) g_rho[lo + t] = fac * sa[t];
-    }
-    if (threadIdx.x == 0) g_rho[0] = 0.0;
+    thomas_block<true>(c, g, cp, dp, g_rho, c.fourpi * (c.dz * c.dz));
 }
 
 // dL/d(parameters of rho_GJ) from the node gradient: knots (hat weights times
