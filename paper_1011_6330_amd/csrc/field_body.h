@@ -5,6 +5,7 @@
 #include <math.h>
 
 #include "pcpic_internal.h"
+#include "push_common.h"
 
 namespace pcpic {
 
@@ -23,7 +24,98 @@ struct FieldArgs {
     int64_t sched_n = 0;
     unsigned long long *hist = nullptr;   // step before a sort: key counts (injected particles added)
     int64_t inj_key = 0;                  // sort key of a particle injected at x = 0, u = 0
+    // fused steps (k_step.hip; sc null: the counters hold the tally and the slot count)
+    StepScratch *sc = nullptr;
+    int w_in = 0, w_add = 0, w_zero = 0;  // sc->w0 of the step that ends, of the one that begins, and to clear
+    int n_in = 0;                         // sc->n of the slot count before the injection; n_in ^ 1 receives the new one
+    int64_t *rec = nullptr;               // receives the slot count after the injection
+    int push = 0;                         // 1: the injected particles also take the step that begins
+    unsigned long long *Jn = nullptr;     //   its current, slots written (X, U: the state before it), and
+    double *Xo = nullptr, *Uo = nullptr;  //   key counts when a sort follows it
+    unsigned long long *push_hist = nullptr;
+    double u_hi = 0.0;
 };
+
+// The first step of the n particles just injected at x = 0, u = 0, which all move
+// alike: the push of one (push_one_f64's or push_one_lo's expressions at x = 0),
+// its deposit and tallies times n, and the slots [base, base + n) written by the
+// bs threads of the block.  ez0: E_z at face 0.
+__device__ __forceinline__ void push_injected(const Consts &c, const FieldArgs &a, double ez0, long long base,
+                                              long long n, int bs)
+{
+    if (n <= 0) return;
+    double x1, u1, F1;
+    float o1 = 0.0f, uf1 = 0.0f;
+    int c1;
+    bool fin;
+    if (a.CL) {
+        const float E = (float)(c.qmdt * ez0);
+        uf1 = 0.0f + E;
+        float t = uf1 * uf1;
+        t = 1.0f + t;
+        const float v = uf1 * __builtin_amdgcn_rsqf(t);
+        o1 = 0.0f + (float)c.dtdz * v;
+        c1 = 0;
+        carry_f32(o1, c1);
+        if (fabsf(uf1) >= f32_at_least(a.u_hi)) {
+            const float q = rintf(o1 * 16777216.0f);
+            const bool up = q >= 16777216.0f;
+            c1 += up ? 1 : 0;
+            o1 = up ? 0.0f : q * 0x1p-24f;
+        }
+        fin = isfinite(uf1) && isfinite(o1);
+        F1 = rint((double)o1 * c.twoP);
+        x1 = 0.0;
+        u1 = (double)uf1;
+    } else {
+        const double E = c.qmdt * ez0;
+        u1 = 0.0 + E;
+        double tt = u1 * u1;
+        tt = 1.0 + tt;
+        double gam, v;
+        gamma_velocity(u1, tt, gam, v);
+        x1 = 0.0 + c.dtdz * v;
+        fin = isfinite(u1) && isfinite(x1);
+        const double c1d = floor(x1);
+        c1 = (int)c1d;
+        F1 = rint((x1 - c1d) * c.twoP);
+    }
+    // |move| < 1 cell from x = 0: cell 0, back to the star, or (an offset rounded up
+    // to 1 on the 2^-24 grid) node 1
+    const bool stays = fin && c1 >= 0;
+    if (threadIdx.x == 0) {
+        const unsigned long long m = (unsigned long long)n;
+        if (fin) {
+            const double va = c1 > 0 ? c.twoP : (c1 < 0 ? 0.0 : F1);
+            if (va != 0.0) atomicAdd(a.Jn, m * (unsigned long long)(long long)va);
+            if (c1 > 0 && c1 < c.N && F1 != 0.0) atomicAdd(a.Jn + c1, m * (unsigned long long)(long long)F1);
+        } else {
+            atomicAdd((unsigned long long *)&a.ctr->n_removed, m);
+            atomicOr(&a.ctr->status, (unsigned long long)PIC_ST_NONFINITE);
+        }
+        if (fin && c1 < 0) {
+            atomicAdd((unsigned long long *)&a.ctr->n_absorb, m);
+            atomicAdd((unsigned long long *)&a.ctr->n_removed, m);
+        }
+        if (stays && c1 == 0) atomicAdd(&a.sc->w0[a.w_add], m * (unsigned long long)(long long)(c.twoP - F1));
+        if (stays && a.push_hist)
+            atomicAdd(a.push_hist + (a.CL ? sort_key_f32(c, c1, o1, fabs(u1) >= a.u_hi) : sort_key_f64(c, x1)), m);
+    }
+    for (long long p = threadIdx.x; p < n; p += bs) {
+        if (a.CL) {
+            a.CL[base + p] = stays ? c1 : -1;
+            a.OL[base + p] = stays ? o1 : 0.0f;
+            a.UL[base + p] = stays ? uf1 : 0.0f;
+        } else {
+            if (a.X != a.Xo) {
+                a.X[base + p] = 0.0;
+                a.U[base + p] = 0.0;
+            }
+            a.Xo[base + p] = stays ? x1 : -1.0;
+            a.Uo[base + p] = stays ? u1 : 0.0;
+        }
+    }
+}
 
 // Leap-frog update of eq. (3) at face i (the update of face N-1 also owns node N):
 //   B_{i+1/2}  <- B - [ (dt/dz)(E_r,i+1 - E_r,i) + (dt/R) E_z,i+1/2 ]
@@ -192,8 +284,10 @@ __device__ __forceinline__ void field_tile(const Consts &c, const FieldArgs &a, 
     DevCounters *ctr = a.ctr;
     if (threadIdx.x == 0) {
         // surface field from the node-0 Gauss law over the half cell [0, dz/2]
-        const int64_t w0 = __hip_atomic_load(&ctr->w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t slots = __hip_atomic_load(&ctr->n_slots, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int64_t *wp = a.sc ? (const int64_t *)&a.sc->w0[a.w_in] : &ctr->w0;
+        const int64_t *np = a.sc ? &a.sc->n[a.n_in] : &ctr->n_slots;
+        const int64_t w0 = __hip_atomic_load(wp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int64_t slots = __hip_atomic_load(np, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // FP32-bulk: the two streams together stay within the capacity, since a
         // sort may move every particle into either one (0 in FP64 mode)
         const int64_t slots_hi = __hip_atomic_load(&ctr->n_slots_hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -229,11 +323,23 @@ __device__ __forceinline__ void field_tile(const Consts &c, const FieldArgs &a, 
         ctr->last_ninj = ninj;
         ctr->e_surf = es;
         ctr->w0_last = w0;
-        ctr->w0 = 0;
+        if (!a.sc) {
+            ctr->w0 = 0;
+        } else if (a.push) {
+            a.sc->n[a.n_in ^ 1] = slots + ninj;
+            a.sc->w0[a.w_zero] = 0;
+        } else {
+            a.sc->w0[0] = a.sc->w0[1] = a.sc->w0[2] = 0;
+        }
+        if (a.rec) *a.rec = slots + ninj;
         ctr->step += 1;
     }
     __syncthreads();
     const long long base = s_base, n = s_n;
+    if (a.push) {
+        push_injected(c, a, s_ez0, base, n, bs);
+        return;
+    }
     for (long long p = threadIdx.x; p < n; p += bs) {
         // electrons leave the surface at rest
         if (a.CL) {

@@ -122,11 +122,6 @@ __global__ __launch_bounds__(256) void k_copy_slots(const double *X, const doubl
     }
 }
 
-__global__ void k_record_slots(const DevCounters *ctr, int64_t *dst)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = ctr->n_slots;
-}
-
 __global__ __launch_bounds__(256) void k_fill_f64(double *p, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.0;
@@ -469,12 +464,6 @@ static inline unsigned gridn(int64_t n) { return (unsigned)((n + 255) / 256); }
 hipError_t launch_copy_slots(pic_handle *h, const double *X, const double *U, double *Xc, double *Uc)
 {
     hipLaunchKernelGGL(k_copy_slots, dim3(h->n_cu * 8), dim3(256), 0, h->stream, X, U, Xc, Uc, h->ws.ctr);
-    return hipGetLastError();
-}
-
-hipError_t launch_record_slots(pic_handle *h, int64_t *dst)
-{
-    hipLaunchKernelGGL(k_record_slots, dim3(1), dim3(64), 0, h->stream, h->ws.ctr, dst);
     return hipGetLastError();
 }
 

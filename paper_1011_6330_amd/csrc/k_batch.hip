@@ -96,6 +96,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_push(BatchArgs b)
                          generic(T.hw[b.pb]), generic(T.hg[b.pb]), generic(T.uh[b.pb]), generic(T.k32),
                          generic(T.ez[b.fb]),
                          (unsigned long long *)generic(T.j[b.jb]), generic(T.ctr),
+                         (unsigned long long *)&generic(T.ctr)->w0,
                          b.hist ? (unsigned long long *)generic(T.cell_count) : nullptr, T.u_hi};
             push_item_f32<BLOCK, NT>(c, a, local, n_lo, n_hi);
         } else {
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_push(BatchArgs b)
             if (tile0 >= n) return;
             PushArgs a{generic(T.x[b.pb]), generic(T.u[b.pb]), generic(T.x[b.pb]), generic(T.u[b.pb]),
                        generic(T.ez[b.fb]), (unsigned long long *)generic(T.j[b.jb]), generic(T.ctr),
-                       b.hist ? (unsigned long long *)generic(T.cell_count) : nullptr};
+                       (unsigned long long *)&generic(T.ctr)->w0, b.hist ? (unsigned long long *)generic(T.cell_count) : nullptr};
             push_tile_f64<BLOCK, PPT, NT>(c, a, n, tile0);
         }
     }
@@ -292,6 +293,7 @@ TubeDev tube_dev(pic_handle *t)
     TubeDev d{};
     const Workspace &w = t->ws;
     d.c = t->c;
+    for (int k = 0; k < 3; ++k) d.j[k] = to_global(w.j[k]);
     for (int k = 0; k < 2; ++k) {
         d.x[k] = to_global(w.x[k]);
         d.u[k] = to_global(w.u[k]);
@@ -305,10 +307,10 @@ TubeDev tube_dev(pic_handle *t)
         d.ez[k] = to_global(w.ez[k]);
         d.er[k] = to_global(w.er[k]);
         d.b[k] = to_global(w.b[k]);
-        d.j[k] = to_global(w.j[k]);
     }
     d.k32 = to_global(w.k32);
     d.ctr = to_global(w.ctr);
+    d.sc = to_global(w.sc);
     d.cell_count = to_global(w.cell_count);
     d.cell_off = to_global(w.cell_off);
     d.total_lo = to_global(w.total_lo);
@@ -378,6 +380,14 @@ static BSortArgs bsort_args(pic_handle *h)
                      1 - t0->pbuf};
 }
 
+// Zero every tube's key counts before the step that accumulates them.
+hipError_t launch_batch_clear(pic_handle *h)
+{
+    if (h->batch_scan_blocks <= 0 || h->batch_scan_blocks > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_bsort_clear, dim3((unsigned)h->batch_scan_blocks), dim3(256), 0, h->stream, bsort_args(h));
+    return hipGetLastError();
+}
+
 // nsteps steps of every tube: the work-list, push and field kernels per step.
 // With hist_last, the key counts are cleared first and the last step's push
 // counts the sort keys of its survivors (the sort that follows skips its
@@ -394,9 +404,8 @@ hipError_t launch_batch_steps(pic_handle *h, int nsteps, bool hist_last, hipEven
     pic_handle *t0 = h->tubes[0];
     const unsigned pgrid = (unsigned)h->batch_push_items, fgrid = (unsigned)h->batch_field_items;
     if (hist_last) {
-        if (h->batch_scan_blocks <= 0 || h->batch_scan_blocks > 0x7fffffff) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_bsort_clear, dim3((unsigned)h->batch_scan_blocks), dim3(256), 0, h->stream,
-                           bsort_args(h));
+        const hipError_t e = launch_batch_clear(h);
+        if (e != hipSuccess) return e;
     }
     const bool f32 = t0->p.precision == PIC_FP32_BULK;
     for (int s = 0; s < nsteps; ++s) {

@@ -268,18 +268,6 @@ hipError_t launch_field_inject(pic_handle *h)
     return hipGetLastError();
 }
 
-// Field update + injection with explicit field buffers and injection target
-// (used by the adjoint recompute; FP64 only).
-hipError_t launch_field_ptrs(pic_handle *h, const double *ezo, const double *ero, const double *bo, double *ezn,
-                             double *ern, double *bn, double *X, double *U)
-{
-    Workspace &w = h->ws;
-    FieldArgs a{ezo, ero, bo, ezn, ern, bn, w.j[h->jbuf], w.j[1 - h->jbuf], nullptr, X, U,
-                nullptr, nullptr, nullptr, w.ctr, h->d_sched, h->sched_first, h->sched_n};
-    hipLaunchKernelGGL(k_field_inject, dim3(grid_for(h->c.N, 256 * FIELD_CPT)), dim3(256), 0, h->stream, h->c, a);
-    return hipGetLastError();
-}
-
 hipError_t launch_check_append(pic_handle *h, int64_t base, int64_t n)
 {
     if (n > 0)

@@ -37,30 +37,12 @@ template <int BLOCK, int PPT, int NT, int GR = 0>
 static hipError_t launch_push_t(pic_handle *h)
 {
     PushArgs a{h->ws.x[h->pbuf], h->ws.u[h->pbuf], h->ws.x[h->pbuf], h->ws.u[h->pbuf], h->ws.ez[h->fbuf],
-               (unsigned long long *)h->ws.j[h->jbuf], h->ws.ctr,
+               (unsigned long long *)h->ws.j[h->jbuf], h->ws.ctr, (unsigned long long *)&h->ws.ctr->w0,
                h->hist_on ? (unsigned long long *)h->ws.cell_count : nullptr};
     const int64_t tile = (int64_t)BLOCK * PPT;
     const unsigned grid = (unsigned)((h->c.cap + tile - 1) / tile);
     hipLaunchKernelGGL((k_push_f64<BLOCK, PPT, NT, GR>), dim3(grid), dim3(BLOCK), 0, h->stream, h->c, a);
     return hipGetLastError();
-}
-
-template <int BLOCK, int PPT, int NT>
-static hipError_t launch_push_args_t(pic_handle *h, const PushArgs &a)
-{
-    const int64_t tile = (int64_t)BLOCK * PPT;
-    const unsigned grid = (unsigned)((h->c.cap + tile - 1) / tile);
-    hipLaunchKernelGGL((k_push_f64<BLOCK, PPT, NT>), dim3(grid), dim3(BLOCK), 0, h->stream, h->c, a);
-    return hipGetLastError();
-}
-
-// FP64 push reading (X, U) and writing (Xo, Uo) in the field ez (used by the
-// adjoint recompute), at the default launch shape.
-hipError_t launch_push_f64_ptrs(pic_handle *h, const double *X, const double *U, double *Xo, double *Uo,
-                                const double *ez)
-{
-    PushArgs a{X, U, Xo, Uo, ez, (unsigned long long *)h->ws.j[h->jbuf], h->ws.ctr};
-    return launch_push_args_t<128, 2, 1>(h, a);
 }
 
 hipError_t launch_push_f64(pic_handle *h)

@@ -208,7 +208,7 @@ static hipError_t launch_push32_t(pic_handle *h)
     const int64_t tile_hi = (int64_t)BLOCK * F32_PPT_HI;
     const unsigned items = (unsigned)((h->c.cap + tile_hi - 1) / tile_hi + 1);   // both streams, any split
     Push32Args a{w.cl[b], w.ol[b], w.ul[b], w.hp[b], w.hw[b], w.hg[b], w.uh[b], w.k32, w.ez[h->fbuf],
-                 (unsigned long long *)w.j[h->jbuf], w.ctr,
+                 (unsigned long long *)w.j[h->jbuf], w.ctr, (unsigned long long *)&w.ctr->w0,
                  h->hist_on ? (unsigned long long *)w.cell_count : nullptr, h->u_hi};
     hipLaunchKernelGGL((k_push_f32<BLOCK, NT>), dim3(items), dim3(BLOCK), 0, h->stream, h->c, a);
     return hipGetLastError();

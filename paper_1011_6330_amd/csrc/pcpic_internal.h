@@ -82,6 +82,10 @@ constexpr int HI_GROUP = 1 << HI_GROUP_LOG2;
 // Steps per captured round of a tube that never sorts (even: the field and
 // current buffers end a round in the parity they started it in).
 constexpr int64_t GRAPH_ROUND = 32;
+// Capacity up to which a tube (all tubes of a batch together) takes fused steps
+// (k_step.hip has the times on both sides of it); an adjoint run always does, as it
+// also saves a kernel per step there that notes the slot count.
+constexpr int64_t FUSE_SLOTS = (int64_t)1 << 22;
 
 // Faces per thread of the field update (field_body.h): a wave takes 256 faces,
 // as two pairs per lane where the flat update applies.
@@ -170,6 +174,14 @@ struct DevCounters {
     int64_t n_slots_hi;                 // FP32-bulk: occupied slots of the high-gamma stream
 };
 
+// State of a run of fused steps (k_step.hip) between its kernels: the slot count
+// that the pushes of a step take (two words in turn) and the node-0 tallies of
+// three steps in turn (all zero between runs).
+struct StepScratch {
+    int64_t n[2];
+    unsigned long long w0[3];
+};
+
 struct Workspace {
     double *x[2], *u[2];    // particle double buffer (FP64)
     // FP32-bulk streams (double-buffered): low (cell, offset, u f32); high (position
@@ -187,12 +199,13 @@ struct Workspace {
     long long *stage_base;      // [2] slot counts of the two streams before the append
     long long *total_lo;    // FP32-bulk sort: low-destination total
     double *ez[2], *er[2], *b[2];
-    int64_t *j[2];          // fixed-point current, ping-pong per step
+    int64_t *j[3];          // fixed-point current: the next step's (clear), the last step's, and a third for fused steps
     double *rho_gj;
     int64_t *w;             // CIC node weights (Poisson, diagnostics)
     double *phi, *cp, *dp, *rhs;
     double *knots;
     DevCounters *ctr;
+    StepScratch *sc;
     // profile bins
     long long *pcount;
     unsigned long long *plo;
@@ -235,9 +248,10 @@ struct TubeDev {
     gptr<int> hg[2];
     gptr<double> uh[2];
     gptr<double> ez[2], er[2], b[2];
-    gptr<int64_t> j[2];
+    gptr<int64_t> j[3];
     gptr<float> k32;
     gptr<DevCounters> ctr;
+    gptr<StepScratch> sc;
     gptr<long long> cell_count, cell_off, total_lo, blk_sum;
     gptr<double> rhs, cp, dp, phi;   // Poisson solve of eq. (4)
     double u_hi;
@@ -304,7 +318,12 @@ struct AdjRecord {
     double loss = 0.0, forward_ms = 0.0;
     int64_t step_end = 0;       // the tube's step count after the forward
     int64_t mut = 0;            // the tube's change count after the forward
-    int jb_final = 0;           // current buffer parity after the forward
+    int jb_final = 0, jl_final = 1;   // current buffers (next, last) after the forward
+};
+
+// Buffers after a captured round.
+struct GraphEnd {
+    int fbuf, jbuf, jlast, pbuf;
 };
 
 struct pic_handle {
@@ -316,7 +335,8 @@ struct pic_handle {
     hipStream_t stream = nullptr;
     int pbuf = 0;       // current particle buffer
     int fbuf = 0;       // field buffer holding E^n, B^{n-1/2}
-    int jbuf = 0;       // current buffer that the next step deposits into
+    int jbuf = 0;       // current buffer that the next step deposits into (0 or 1, clear)
+    int jlast = 1;      // current buffer of the last step
     int64_t step = 0;   // steps enqueued
     int push_block = 64;
     int push_ppt = 2;
@@ -346,10 +366,13 @@ struct pic_handle {
     int64_t *d_scan_pref = nullptr;             // [n + 1] prefix of 1024-key scan blocks
     int32_t *d_field_map = nullptr;             // cell tile -> tube
     int32_t *d_chunk_map = nullptr, *d_scan_map = nullptr;
+    int64_t *d_run_pref = nullptr;              // fused steps: [n + 1] first block of each tube
+    int32_t *d_run_map = nullptr;               //   block -> tube
+    int64_t batch_run_blocks = 0;               //   blocks of a kernel (0: the batch is too large for fused steps)
     int batch_block = 256, batch_ppt = 2;
     int64_t batch_push_items = 0, batch_field_items = 0, batch_sort_items = 0, batch_keys = 0, batch_scan_blocks = 0;
     hipGraphExec_t graph[8] = {};   // one round, keyed by the (field, current, particle) buffer parities
-    int64_t graph_steps = 0;
+    GraphEnd graph_end[8] = {};
     bool use_graph = true;
 };
 
@@ -363,10 +386,27 @@ hipError_t launch_fields_from_phi(pic_handle *h);
 hipError_t launch_thomas_batch(pic_handle *b, const int32_t *d_list, int n);
 hipError_t launch_push_f64(pic_handle *h);
 hipError_t launch_push_f32(pic_handle *h);
-hipError_t launch_push_f64_ptrs(pic_handle *h, const double *X, const double *U, double *Xo, double *Uo,
-                                const double *ez);
-hipError_t launch_field_ptrs(pic_handle *h, const double *ezo, const double *ero, const double *bo, double *ezn,
-                             double *ern, double *bn, double *X, double *U);
+// Fused steps (k_step.hip).  Fields before (ez, er, b) and after (ezn, ern, bn) the
+// field update a kernel makes, slots its push reads (X, U) and writes (Xo, Uo).
+struct RunPtrs {
+    const double *ez, *er, *b;
+    double *ezn, *ern, *bn;
+    double *X, *U, *Xo, *Uo;
+};
+// Kernel s of a run (s = 1: the push of the first step; s > 1: the field update of
+// step s - 1 and the push of step s), the closing field update of a run of m steps
+// (which moves the tube's current buffers on), and a whole run in place.
+hipError_t launch_run_step(pic_handle *h, int64_t s, const RunPtrs &r, bool hist, int64_t *rec);
+hipError_t launch_run_end(pic_handle *h, int64_t m, const RunPtrs &r, bool hist, int64_t *rec);
+hipError_t launch_run(pic_handle *h, int64_t m, bool hist_last, int64_t *rec = nullptr);
+// The same for a batch; blocks of one of its tubes in a run's kernels.
+hipError_t launch_batch_run(pic_handle *h, int64_t m, bool hist_last);
+int64_t run_blocks(const pic_params &p);
+// Current buffers of a run that starts with jb clear: step s (from 1) adds to
+// run_j(jb, s); after m steps run_j(jb, m) holds the last current and run_next(jb, m)
+// is clear.
+inline int run_j(int jb, int64_t s) { return (s - 1) % 3 == 0 ? jb : ((s - 1) % 3 == 1 ? 2 : 1 - jb); }
+inline int run_next(int jb, int64_t m) { return run_j(jb, m) == jb ? 1 - jb : jb; }
 // Profile bins: count, 128-bit sum (low and high words), ordered bit images of min and max.
 struct ProfPtrs {
     long long *cnt;
@@ -396,13 +436,13 @@ hipError_t launch_append_staged(pic_handle *h, int64_t n, bool check_only);
 hipError_t launch_scan(pic_handle *h, int64_t n_keys);
 hipError_t launch_batch_steps(pic_handle *h, int nsteps, bool hist_last, hipEvent_t *ev = nullptr);
 hipError_t launch_copy_slots(pic_handle *h, const double *X, const double *U, double *Xc, double *Uc);
-hipError_t launch_record_slots(pic_handle *h, int64_t *dst);
 hipError_t launch_zero_f64(pic_handle *h, double *p, int64_t n);
 hipError_t launch_adj_step(pic_handle *h, const AdjStepPtrs &s);
 hipError_t launch_adj_finish(pic_handle *h, const double *lez, const double *ler, double *gphi, double *cp,
                              double *dp, double *g_rho, double *params);
 hipError_t launch_zero_i64(pic_handle *h, int64_t *p, int64_t n);
 hipError_t launch_batch_sort(pic_handle *h, bool hist_ready);
+hipError_t launch_batch_clear(pic_handle *h);
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t n16, hipStream_t stream);
 bool batch_shape_supported(pic_handle *h);
 TubeDev tube_dev(pic_handle *t);

@@ -327,6 +327,7 @@ Workspace carve(const pic_params &p, uint8_t *base)
         w.b[k] = (double *)take(N * 8);
         w.j[k] = (int64_t *)take(N * 8);
     }
+    w.j[2] = (int64_t *)take(N * 8);
     w.rho_gj = (double *)take((N + 1) * 8);
     w.w = (int64_t *)take((N + 1) * 8);
     w.phi = (double *)take((N + 1) * 8);
@@ -335,6 +336,7 @@ Workspace carve(const pic_params &p, uint8_t *base)
     w.rhs = (double *)take((N + 1) * 8);
     w.knots = (double *)take((size_t)(p.n_knots > 0 ? p.n_knots : 1) * 8);
     w.ctr = (DevCounters *)take(sizeof(DevCounters));
+    w.sc = (StepScratch *)take(sizeof(StepScratch));
     w.pcount = (long long *)take(nb * 8);
     w.plo = (unsigned long long *)take(nb * 8);
     w.phi128 = (long long *)take(nb * 8);
@@ -510,6 +512,7 @@ static pic_status init_tube(const pic_params *p, void *d_workspace, size_t ws_by
         return fail(PIC_EDEVICE, "%s: %s", what, hipGetErrorString(e));
     };
     hipError_t e = hipMemsetAsync(h->ws.ctr, 0, sizeof(DevCounters), h->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(h->ws.sc, 0, sizeof(StepScratch), h->stream);
     if (e != hipSuccess) return bail(e, "clear counters");
     if (!h->knots.empty()) {
         e = hipMemcpyAsync(h->ws.knots, h->knots.data(), h->knots.size() * 8, hipMemcpyHostToDevice, h->stream);
@@ -616,20 +619,31 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
 static pic_status batch_status(pic_handle *h);
 static void free_batch_graphs(pic_handle *h);
 
-// One step of a single tube, launched directly: push (counting the sort keys
-// on the step before a sort), field update + injection, and the sort.
-static pic_status tube_step_direct(pic_handle *h)
+// Small tubes take their steps in fused runs (k_step.hip).
+static bool fused(const pic_handle *h) { return h->c.cap <= FUSE_SLOTS && !(h->c.flags & PIC_GR_ALPHA); }
+
+// m steps of a single tube, launched directly, of which only the last may be
+// followed by a sort (its push counts the sort keys): fused, or step by step push
+// and field update + injection.
+static pic_status tube_steps_direct(pic_handle *h, int64_t m)
 {
-    const bool sort_after = h->p.sort_every > 0 && (h->step + 1) % h->p.sort_every == 0;
+    const bool sort_after = h->p.sort_every > 0 && (h->step + m) % h->p.sort_every == 0;
     if (sort_after) HIP_OK(launch_clear_hist(h));
-    h->hist_on = sort_after;            // the step counts the sort keys of its survivors
-    hipError_t e1 = launch_push(h);
-    hipError_t e2 = e1 == hipSuccess ? launch_field_inject(h) : e1;
-    h->hist_on = false;
-    HIP_OK(e2);
-    h->fbuf ^= 1;
-    h->jbuf ^= 1;
-    h->step += 1;
+    if (m > 1 && fused(h)) {
+        HIP_OK(launch_run(h, m, sort_after));
+    } else {
+        for (int64_t s = 0; s < m; ++s) {
+            h->hist_on = sort_after && s == m - 1;
+            hipError_t e1 = launch_push(h);
+            hipError_t e2 = e1 == hipSuccess ? launch_field_inject(h) : e1;
+            h->hist_on = false;
+            HIP_OK(e2);
+            h->fbuf ^= 1;
+            h->jlast = h->jbuf;
+            h->jbuf ^= 1;
+        }
+    }
+    h->step += m;
     if (sort_after) HIP_OK(launch_sort(h, true));
     return PIC_OK;
 }
@@ -661,13 +675,13 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
         if (S > 1 && h->use_graph && h->step % S == 0 && n_steps >= S) {
             const int key = h->fbuf | (h->jbuf << 1) | (h->pbuf << 2);
             if (!h->graph[key]) {
-                const int fb = h->fbuf, jb = h->jbuf, pb = h->pbuf;
+                const int fb = h->fbuf, jb = h->jbuf, jl = h->jlast, pb = h->pbuf;
                 const int64_t st = h->step;
                 hipGraph_t g = nullptr;
                 bool ok = hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
                 if (ok) {
-                    pic_status rc = PIC_OK;
-                    for (int64_t s = 0; s < S && rc == PIC_OK; ++s) rc = tube_step_direct(h);
+                    const pic_status rc = tube_steps_direct(h, S);
+                    h->graph_end[key] = GraphEnd{h->fbuf, h->jbuf, h->jlast, h->pbuf};
                     const hipError_t e = hipStreamEndCapture(h->stream, &g);
                     ok = rc == PIC_OK && e == hipSuccess && g &&
                          hipGraphInstantiate(&h->graph[key], g, nullptr, nullptr, 0) == hipSuccess;
@@ -676,6 +690,7 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
                 // the captured round has not run yet
                 h->fbuf = fb;
                 h->jbuf = jb;
+                h->jlast = jl;
                 h->pbuf = pb;
                 h->step = st;
                 if (!ok) {
@@ -686,14 +701,17 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
                 }
             }
             HIP_OK(hipGraphLaunch(h->graph[key], h->stream));
-            h->fbuf ^= (int)(S & 1);
-            h->jbuf ^= (int)(S & 1);
-            if (sorts) h->pbuf ^= 1;
+            const GraphEnd &g = h->graph_end[key];
+            h->fbuf = g.fbuf;
+            h->jbuf = g.jbuf;
+            h->jlast = g.jlast;
+            h->pbuf = g.pbuf;
             h->step += S;
             n_steps -= S;
         } else {
-            if (pic_status rc = tube_step_direct(h)) return rc;
-            n_steps -= 1;
+            const int64_t left = S - h->step % S, m = n_steps < left ? n_steps : left;
+            if (pic_status rc = tube_steps_direct(h, m)) return rc;
+            n_steps -= m;
         }
     }
     return PIC_OK;
@@ -766,6 +784,7 @@ pic_status pic_step_timed(pic_handle *h, int64_t n_steps, pic_timing *out)
             break;
         }
         h->fbuf ^= 1;
+        h->jlast = h->jbuf;
         h->jbuf ^= 1;
         h->step += 1;
         const bool sorted = sort_after;
@@ -917,7 +936,7 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
                           {out->er, w.er[f], (size_t)(N + 1) * 8},
                           {out->b_phi, w.b[f], (size_t)N * 8},
                           {out->rho_gj, w.rho_gj, (size_t)(N + 1) * 8},
-                          {out->j_last, w.j[1 - h->jbuf], (size_t)N * 8},
+                          {out->j_last, w.j[h->jlast], (size_t)N * 8},
                           {out->weights, w.w, (size_t)(N + 1) * 8},
                           {gdst, w.gauss, (size_t)(N + 1) * 8}};
     Want packed[13];
@@ -1231,7 +1250,7 @@ pic_status pic_save(pic_handle *h, void *buf, size_t cap, size_t *bytes)
     HIP_OK(d2h(L.ez, w.ez[f], (size_t)N * 8));
     HIP_OK(d2h(L.er, w.er[f], (size_t)(N + 1) * 8));
     HIP_OK(d2h(L.b, w.b[f], (size_t)N * 8));
-    HIP_OK(d2h(L.j, w.j[1 - h->jbuf], (size_t)N * 8));
+    HIP_OK(d2h(L.j, w.j[h->jlast], (size_t)N * 8));
     if (!f32) {
         HIP_OK(d2h(L.p[0], w.x[b], (size_t)nlo * 8));
         HIP_OK(d2h(L.p[1], w.u[b], (size_t)nlo * 8));
@@ -1297,7 +1316,7 @@ pic_status pic_load(pic_handle *h, const void *buf, size_t bytes)
     HIP_OK(h2d(w.ez[f], L.ez, (size_t)N * 8));
     HIP_OK(h2d(w.er[f], L.er, (size_t)(N + 1) * 8));
     HIP_OK(h2d(w.b[f], L.b, (size_t)N * 8));
-    HIP_OK(h2d(w.j[1 - h->jbuf], L.j, (size_t)N * 8));
+    HIP_OK(h2d(w.j[h->jlast], L.j, (size_t)N * 8));
     HIP_OK(launch_zero_i64(h, w.j[h->jbuf], N));        // the next step deposits into a cleared J
     if (!f32) {
         HIP_OK(h2d(w.x[b], L.p[0], (size_t)hd.n_lo * 8));
@@ -1359,11 +1378,13 @@ pic_status pic_destroy(pic_handle *h)
 struct BatchMapSizes {
     int64_t push;   // push items at the smallest tile (64 threads x 2 slots), the work list's bound
     int64_t field, chunk, scan;
+    int64_t run;    // blocks of the fused steps' kernels (0: too many slots for them)
 };
 
 static BatchMapSizes batch_map_sizes(const pic_params *tubes, int n)
 {
-    BatchMapSizes m{0, 0, 0, 0};
+    BatchMapSizes m{0, 0, 0, 0, 0};
+    int64_t slots = 0;
     for (int t = 0; t < n; ++t) {
         const pic_params &p = tubes[t];
         const bool f32 = p.precision == PIC_FP32_BULK;
@@ -1372,7 +1393,10 @@ static BatchMapSizes batch_map_sizes(const pic_params *tubes, int n)
         m.chunk += (p.capacity + SORT_TILE - 1) / SORT_TILE + (f32 ? 1 : 0);
         const int64_t keys = (f32 ? 2 * (p.n_cells + 1) : p.n_cells) << sort_sub_log2(p);
         m.scan += (keys + SORT_SCAN_TILE - 1) / SORT_SCAN_TILE;
+        slots += p.capacity;
     }
+    if (slots <= FUSE_SLOTS)
+        for (int t = 0; t < n; ++t) m.run += run_blocks(tubes[t]);
     return m;
 }
 
@@ -1388,6 +1412,8 @@ static size_t batch_header_bytes(const pic_params *tubes, int n)
     off = align_up(off) + 4 * (size_t)m.chunk;
     off = align_up(off) + 4 * (size_t)m.scan;
     off = align_up(off) + 4 * (size_t)n;   // tubes to solve together
+    off = align_up(off) + sizeof(int64_t) * (size_t)(n + 1);
+    off = align_up(off) + 4 * (size_t)m.run;
     return align_up(off);
 }
 
@@ -1460,6 +1486,16 @@ static pic_status batch_configure(pic_handle *h, int block, int per_thread)
         for (int64_t i = sp[(size_t)t]; i < sp[(size_t)t + 1]; ++i) sm[(size_t)i] = t;
         for (int64_t i = cp[(size_t)t]; i < cp[(size_t)t + 1]; ++i) cm[(size_t)i] = t;
     }
+    std::vector<int64_t> rp((size_t)n + 1, 0);
+    std::vector<int32_t> rm((size_t)h->batch_run_blocks);
+    if (h->batch_run_blocks > 0) {
+        for (int t = 0; t < n; ++t) {
+            rp[(size_t)t + 1] = rp[(size_t)t] + run_blocks(h->tubes[(size_t)t]->p);
+            for (int64_t i = rp[(size_t)t]; i < rp[(size_t)t + 1]; ++i) rm[(size_t)i] = t;
+        }
+        HIP_OK(hipMemcpyAsync(h->d_run_pref, rp.data(), 8 * rp.size(), hipMemcpyHostToDevice, h->stream));
+        HIP_OK(hipMemcpyAsync(h->d_run_map, rm.data(), 4 * rm.size(), hipMemcpyHostToDevice, h->stream));
+    }
     HIP_OK(hipMemcpyAsync(h->d_field_map, fm.data(), 4 * fm.size(), hipMemcpyHostToDevice, h->stream));
     HIP_OK(hipMemcpyAsync(h->d_chunk_map, sm.data(), 4 * sm.size(), hipMemcpyHostToDevice, h->stream));
     HIP_OK(hipMemcpyAsync(h->d_scan_map, cm.data(), 4 * cm.size(), hipMemcpyHostToDevice, h->stream));
@@ -1514,6 +1550,9 @@ pic_status pic_init_batch(const pic_params *tubes, int32_t n_tubes, void *d_work
         h->d_chunk_map = (int32_t *)take(4 * (size_t)m.chunk);
         h->d_scan_map = (int32_t *)take(4 * (size_t)m.scan);
         h->d_pending = (int32_t *)take(4 * (size_t)n_tubes);
+        h->d_run_pref = (int64_t *)take(8 * (size_t)(n_tubes + 1));
+        h->d_run_map = (int32_t *)take(4 * (size_t)m.run);
+        h->batch_run_blocks = m.run;
     }
     off = batch_header_bytes(tubes, n_tubes);
     for (int t = 0; t < n_tubes; ++t) {
@@ -1590,17 +1629,18 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
             r = n < 64 ? n : 64;
         }
         const bool to_sort = S > 0 && (t0->step + r) % S == 0;
+        const bool run = h->batch_run_blocks > 0 && r > 1 && !ev;   // fused steps (timed runs measure push and field apart)
         const int key = t0->fbuf | (t0->jbuf << 1) | (t0->pbuf << 2);
         const bool round = to_sort && r == S && h->use_graph && !ev;
         if (round && !h->graph[key]) {
             hipGraph_t g = nullptr;
             if (hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-                hipError_t e1 = launch_batch_steps(h, (int)r, true);
+                hipError_t e1 = run ? launch_batch_clear(h) : launch_batch_steps(h, (int)r, true);
+                if (run && e1 == hipSuccess) e1 = launch_batch_run(h, r, true);
                 hipError_t e2 = launch_batch_sort(h, true);
                 hipError_t e3 = hipStreamEndCapture(h->stream, &g);
                 if (e1 == hipSuccess && e2 == hipSuccess && e3 == hipSuccess && g &&
                     hipGraphInstantiate(&h->graph[key], g, nullptr, nullptr, 0) == hipSuccess) {
-                    h->graph_steps = r;
                 } else {
                     h->graph[key] = nullptr;
                     h->use_graph = false;
@@ -1622,7 +1662,12 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
                 e = &(*ev)[ev->size() - ne];
                 for (size_t k = 0; k < ne; ++k) HIP_OK(hipEventCreate(&e[k]));
             }
-            HIP_OK(launch_batch_steps(h, (int)r, to_sort, e));
+            if (run) {
+                if (to_sort) HIP_OK(launch_batch_clear(h));
+                HIP_OK(launch_batch_run(h, r, to_sort));
+            } else {
+                HIP_OK(launch_batch_steps(h, (int)r, to_sort, e));
+            }
             if (e) HIP_OK(hipEventRecord(e[ne - 2], h->stream));
             if (to_sort) HIP_OK(launch_batch_sort(h, true));
             if (e) HIP_OK(hipEventRecord(e[ne - 1], h->stream));
@@ -1635,7 +1680,8 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
         }
         for (pic_handle *t : h->tubes) {
             t->fbuf ^= (int)(r & 1);
-            t->jbuf ^= (int)(r & 1);
+            t->jlast = run ? run_j(t->jbuf, r) : (t->jbuf ^ (int)((r - 1) & 1));
+            t->jbuf = run ? run_next(t->jbuf, r) : (t->jbuf ^ (int)(r & 1));
             t->step += r;
             if (to_sort) t->pbuf ^= 1;
         }
@@ -1779,9 +1825,9 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
     pic_status s = read_counters(h, &c0);
     if (s != PIC_OK) return done(s);
     FWD_OK(hipEventRecord(ev[0], h->stream));
-    for (int64_t st = 0; st < T; ++st) {
-        if (st % K == 0) {
-            const int64_t ck = st / K;
+    for (int64_t st = 0; st < T; st += K) {
+        const int64_t ck = st / K, m = T - st < K ? T - st : K;
+        {
             const int f = h->fbuf;
             FWD_OK(launch_copy_slots(h, w.x[h->pbuf], w.u[h->pbuf], t.ck_x[ck], t.ck_u[ck]));
             FWD_OK(hipMemcpyAsync(t.ck_ez[ck], w.ez[f], (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
@@ -1789,17 +1835,13 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
             FWD_OK(hipMemcpyAsync(t.ck_b[ck], w.b[f], (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
             FWD_OK(hipMemcpyAsync(t.ck_ctr[ck], w.ctr, sizeof(DevCounters), hipMemcpyDeviceToDevice, h->stream));
         }
-        FWD_OK(launch_record_slots(h, t.nslots + st));
-        FWD_OK(launch_push_f64(h));
-        FWD_OK(launch_field_inject(h));
-        h->fbuf ^= 1;
-        h->jbuf ^= 1;
-        h->step += 1;
+        // a fused run of the segment's steps, whose kernels note the slot counts
+        FWD_OK(launch_run(h, m, false, t.nslots + st));
+        h->step += m;
     }
-    FWD_OK(launch_record_slots(h, t.nslots + T));
     // keep what the recompute overwrites: counters and the last step's current
     FWD_OK(hipMemcpyAsync(t.final_ctr, w.ctr, sizeof(DevCounters), hipMemcpyDeviceToDevice, h->stream));
-    FWD_OK(hipMemcpyAsync(t.final_jlast, w.j[1 - h->jbuf], (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
+    FWD_OK(hipMemcpyAsync(t.final_jlast, w.j[h->jlast], (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
     FWD_OK(hipEventRecord(ev[1], h->stream));
     DevCounters c1;
     s = read_counters(h, &c1);
@@ -1825,6 +1867,7 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
     r.step_end = h->step;
     r.mut = h->mut;
     r.jb_final = h->jbuf;
+    r.jl_final = h->jlast;
     r.forward_ms = fms;
     return done(PIC_OK);
 }
@@ -1899,17 +1942,25 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
         hipError_t e = hipMemcpyAsync(w.ctr, t.ck_ctr[ck], sizeof(DevCounters), hipMemcpyDeviceToDevice, rec_s);
         if (e == hipSuccess) e = launch_zero_i64(h, w.j[0], N);
         if (e == hipSuccess) e = launch_zero_i64(h, w.j[1], N);
-        for (int64_t k = 0; k + 1 < m && e == hipSuccess; ++k) {
-            const double *xi = k == 0 ? t.ck_x[ck] : t.sg_x[q][(size_t)k];
-            const double *ui = k == 0 ? t.ck_u[ck] : t.sg_u[q][(size_t)k];
-            const double *ezo = k == 0 ? t.ck_ez[ck] : t.sg_ez[q][(size_t)k];
-            const double *ero = k == 0 ? t.ck_er[ck] : t.sg_er[q][(size_t)k];
-            const double *bo = k == 0 ? t.ck_b[ck] : t.sg_b[q][(size_t)k];
-            e = launch_push_f64_ptrs(h, xi, ui, t.sg_x[q][(size_t)k + 1], t.sg_u[q][(size_t)k + 1], ezo);
-            if (e == hipSuccess)
-                e = launch_field_ptrs(h, ezo, ero, bo, t.sg_ez[q][(size_t)k + 1], t.sg_er[q][(size_t)k + 1],
-                                      t.sg_b[q][(size_t)k + 1], t.sg_x[q][(size_t)k + 1], t.sg_u[q][(size_t)k + 1]);
-            h->jbuf ^= 1;
+        // a fused run of the segment's steps but the last: kernel s pushes from slot
+        // s-1 to slot s and makes the field update from slot s-2 to slot s-1
+        h->jbuf = 0;
+        h->jlast = 1;
+        auto X = [&](int64_t k) { return k == 0 ? t.ck_x[ck] : t.sg_x[q][(size_t)k]; };
+        auto U = [&](int64_t k) { return k == 0 ? t.ck_u[ck] : t.sg_u[q][(size_t)k]; };
+        auto EZ = [&](int64_t k) { return k == 0 ? t.ck_ez[ck] : t.sg_ez[q][(size_t)k]; };
+        auto ER = [&](int64_t k) { return k == 0 ? t.ck_er[ck] : t.sg_er[q][(size_t)k]; };
+        auto B = [&](int64_t k) { return k == 0 ? t.ck_b[ck] : t.sg_b[q][(size_t)k]; };
+        for (int64_t s = 1; m > 1 && s <= m && e == hipSuccess; ++s) {
+            const int64_t o = s > 1 ? s - 2 : 0, n = s > 1 ? s - 1 : 0;
+            RunPtrs p{EZ(o), ER(o), B(o), EZ(n), ER(n), B(n), X(s - 1), U(s - 1), nullptr, nullptr};
+            if (s < m) {
+                p.Xo = X(s);
+                p.Uo = U(s);
+                e = launch_run_step(h, s, p, false, nullptr);
+            } else {
+                e = launch_run_end(h, m - 1, p, false, nullptr);
+            }
         }
         h->stream = main_s;
         if (e == hipSuccess) e = hipEventRecord(sev[1 + q], rec_s);
@@ -1944,8 +1995,9 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
     // restore the end state the forward left
     ADJ_OK(hipMemcpyAsync(w.ctr, t.final_ctr, sizeof(DevCounters), hipMemcpyDeviceToDevice, h->stream));
     h->jbuf = r.jb_final;
+    h->jlast = r.jl_final;
     ADJ_OK(launch_zero_i64(h, w.j[h->jbuf], N));
-    ADJ_OK(hipMemcpyAsync(w.j[1 - h->jbuf], t.final_jlast, (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
+    ADJ_OK(hipMemcpyAsync(w.j[h->jlast], t.final_jlast, (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
     // results
     std::vector<double> params((size_t)h->c.n_knots + 2);
     double grate = 0.0;

@@ -24,12 +24,14 @@ struct DepAcc {
     int cf;                    // cell of the thread's first deposit (-2 = none yet)
     double am, a0, ap, a2;     // faces cf-1, cf, cf+1, cf+2 (particles starting in cf or cf+1)
     DevCounters *ctr;          // the boundary tallies go straight to the counters
+    unsigned long long *w0;    // and the node-0 weight to its tally
 
-    __device__ __forceinline__ void init(DevCounters *counters)
+    __device__ __forceinline__ void init(DevCounters *counters, unsigned long long *node0_tally)
     {
         cf = -2;
         am = a0 = ap = a2 = 0.0;
         ctr = counters;
+        w0 = node0_tally;
     }
 
     // Boundary events are rare (a few hundred particles per step leave or
@@ -57,7 +59,7 @@ struct DepAcc {
     }
     __device__ __forceinline__ void node0(double w)
     {
-        atomicAdd((unsigned long long *)&ctr->w0, (unsigned long long)(long long)w);
+        atomicAdd(w0, (unsigned long long)(long long)w);
     }
 
     // J_{i+1/2} += S_i(x^n) - S_i(x^{n+1}) for a move from (c0, F0) to (c1, F1),
@@ -193,6 +195,17 @@ __device__ __forceinline__ void gamma_velocity(double u, double tt, double &gam,
         gam = sqrt(tt);
         v = u / gam;
     }
+}
+
+// Offset update with the carry into the next or previous cell (|move| < 1 cell),
+// with selects.  An offset that rounds to 1.0f is stored as (cell + 1, 0).
+__device__ __forceinline__ void carry_f32(float &o, int &cell)
+{
+    const bool up = o >= 1.0f, dn = o < 0.0f;
+    const float om = o + 1.0f;
+    const bool dn_full = dn && om >= 1.0f;       // -tiny + 1 rounds to 1: stays in the cell at 0
+    o = up ? o - 1.0f : (dn ? (dn_full ? 0.0f : om) : o);
+    cell += up ? 1 : ((dn && !dn_full) ? -1 : 0);
 }
 
 typedef double dvec2 __attribute__((ext_vector_type(2)));
