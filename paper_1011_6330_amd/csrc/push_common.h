@@ -67,7 +67,18 @@ struct DepAcc {
     // face i+1/2 (2^P left of node i, 2^P - F in cell i, 0 right of node i+1):
     // face c0 gets (2^P if c1 > c0, 0 if c1 < c0, F1 if c1 = c0) - F0, and a
     // crossed face c1 inside the tube gets F1 (moving right) or F1 - 2^P (left).
-    // Written with selects for a lane that may have nothing to deposit
+    // deposit_direct adds them straight to J.
+    __device__ __forceinline__ static void deposit_direct(unsigned long long *J, int N, double twoP, int c0, double F0,
+                                                          int c1, double F1)
+    {
+        const bool right = c1 > c0, left = c1 < c0;
+        const double va = (right ? twoP : (left ? 0.0 : F1)) - F0;
+        const double vb = left ? F1 - twoP : F1;
+        if (va != 0.0) atomic_add_face(J, c0, va);
+        if (((right && c1 < N) || (left && c1 >= 0)) && vb != 0.0) atomic_add_face(J, c1, vb);
+    }
+
+    // The same with selects for a lane that may have nothing to deposit
     // (ok = false): lanes of a wave split between staying in their cell and
     // crossing a face, and selects keep them on one path.  A particle starting
     // in cf or cf+1 lands in the four channels; any other (a thread whose slots
