@@ -291,7 +291,9 @@ enum {
  * threads); a thread takes per_thread/2 pairs of consecutive slots, 2*block
  * slots apart.  FP32-bulk: 4 (4 consecutive low-stream slots per thread; in
  * the high stream two pairs of slots 128 apart).  pic_init sets 128 x 2 (FP64) or
- * 128 x 4 (FP32-bulk), both with PIC_PUSH_NONTEMPORAL.
+ * 128 x 4 (FP32-bulk), with PIC_PUSH_NONTEMPORAL where the particle streams at
+ * capacity take more than 1 GiB.  Tubes small enough for fused steps (k_step.hip)
+ * have one shape of their own there.
  * Results do not depend on the choice (integer deposition); the autotuner
  * picks the fastest.  Errors: PIC_EINVAL for an unsupported shape or flag. */
 pic_status pic_set_push_config(pic_handle *h, int32_t block, int32_t per_thread, uint32_t flags);

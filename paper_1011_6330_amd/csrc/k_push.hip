@@ -24,12 +24,15 @@
 
 namespace pcpic {
 
+// rev: the tiles in descending order (push_order); the idle blocks come last either way.
 template <int BLOCK, int PPT, int NT, int GR = 0>
-__global__ __launch_bounds__(BLOCK) void k_push_f64(Consts c, PushArgs a)
+__global__ __launch_bounds__(BLOCK) void k_push_f64(Consts c, PushArgs a, int rev)
 {
+    constexpr int64_t TILE = BLOCK * PPT;
     const int64_t n = a.ctr->n_slots;
-    const int64_t tile0 = (int64_t)blockIdx.x * (BLOCK * PPT);
-    if (tile0 >= n) return;                       // whole block idle (uniform)
+    const int64_t k = blockIdx.x;
+    if (k * TILE >= n) return;                    // whole block idle (uniform)
+    const int64_t tile0 = (rev ? (n - 1) / TILE - k : k) * TILE;
     push_tile_f64<BLOCK, PPT, NT, GR>(c, a, n, tile0);
 }
 
@@ -41,14 +44,14 @@ static hipError_t launch_push_t(pic_handle *h)
                h->hist_on ? (unsigned long long *)h->ws.cell_count : nullptr};
     const int64_t tile = (int64_t)BLOCK * PPT;
     const unsigned grid = (unsigned)((h->c.cap + tile - 1) / tile);
-    hipLaunchKernelGGL((k_push_f64<BLOCK, PPT, NT, GR>), dim3(grid), dim3(BLOCK), 0, h->stream, h->c, a);
+    hipLaunchKernelGGL((k_push_f64<BLOCK, PPT, NT, GR>), dim3(grid), dim3(BLOCK), 0, h->stream, h->c, a, push_order(h));
     return hipGetLastError();
 }
 
 hipError_t launch_push_f64(pic_handle *h)
 {
     // PIC_GR_ALPHA: one launch shape (the default), whatever the configured one
-    if (h->c.flags & PIC_GR_ALPHA) return launch_push_t<128, 2, 1, 1>(h);
+    if (h->c.flags & PIC_GR_ALPHA) return h->push_nt ? launch_push_t<128, 2, 1, 1>(h) : launch_push_t<128, 2, 0, 1>(h);
     const int B = h->push_block, P = h->push_ppt;
     if (h->push_nt) {
         if (B == 256 && P == 2) return launch_push_t<256, 2, 1>(h);

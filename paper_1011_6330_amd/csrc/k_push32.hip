@@ -23,10 +23,16 @@
 
 namespace pcpic {
 
+// rev: the items in descending order (push_order); the idle blocks come last either way.
 template <int BLOCK, int NT>
-__global__ __launch_bounds__(BLOCK) void k_push_f32(Consts c, Push32Args a)
+__global__ __launch_bounds__(BLOCK) void k_push_f32(Consts c, Push32Args a, int rev)
 {
-    push_item_f32<BLOCK, NT>(c, a, blockIdx.x, a.ctr->n_slots, a.ctr->n_slots_hi);
+    constexpr int64_t SPAN = (int64_t)BLOCK * F32_PPT_LO;
+    static_assert(F32_PPT_LO == F32_PPT_HI, "one item size for both streams");
+    const int64_t n_lo = a.ctr->n_slots, n_hi = a.ctr->n_slots_hi;
+    const int64_t items = (n_lo + SPAN - 1) / SPAN + (n_hi + SPAN - 1) / SPAN, k = blockIdx.x;
+    if (k >= items) return;
+    push_item_f32<BLOCK, NT>(c, a, rev ? items - 1 - k : k, n_lo, n_hi);
 }
 
 // ------------------------------------------------------------------------
@@ -210,7 +216,7 @@ static hipError_t launch_push32_t(pic_handle *h)
     Push32Args a{w.cl[b], w.ol[b], w.ul[b], w.hp[b], w.hw[b], w.hg[b], w.uh[b], w.k32, w.ez[h->fbuf],
                  (unsigned long long *)w.j[h->jbuf], w.ctr, (unsigned long long *)&w.ctr->w0,
                  h->hist_on ? (unsigned long long *)w.cell_count : nullptr, h->u_hi};
-    hipLaunchKernelGGL((k_push_f32<BLOCK, NT>), dim3(items), dim3(BLOCK), 0, h->stream, h->c, a);
+    hipLaunchKernelGGL((k_push_f32<BLOCK, NT>), dim3(items), dim3(BLOCK), 0, h->stream, h->c, a, push_order(h));
     return hipGetLastError();
 }
 
