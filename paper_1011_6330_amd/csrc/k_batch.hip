@@ -133,7 +133,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_field(BatchArgs b)
 }
 
 // ------------------------------------------------------------------------
-// batched counting sort (per tube: histogram -> scan -> scatter -> finish)
+// batched counting sort (per tube: scan -> scatter)
 // ------------------------------------------------------------------------
 
 struct BSortArgs {
@@ -168,83 +168,31 @@ __device__ __forceinline__ Streams tube_streams(const TubeDev &T, int b)
                    generic(T.hg[b]), generic(T.uh[b])};
 }
 
-// One block per sort item (a tile of SORT_TILE slots of one stream) of a tube.
-__global__ __launch_bounds__(SORT_BLOCK) void k_bsort_hist(BSortArgs a)
+// The passes of sort_body.h, a block never spanning two tubes.
+__device__ __forceinline__ ScanTube scan_tube(const BSortArgs &a, const TubeDev &T)
 {
-    const int64_t it = blockIdx.x;
-    const int t = a.chunk_map[it];
-    const TubeDev &T = a.tubes[t];
-    const Consts c = T.c;
-    bool hi;
-    int64_t tile0, n;
-    if (!sort_item(it - a.chunk_pref[t], a.f32 != 0, generic(T.ctr), hi, tile0, n)) return;
-    hist_tile(c, a.f32 != 0, hi, generic(T.x[a.src]), tube_streams(T, a.src), T.u_hi,
-              (unsigned long long *)generic(T.cell_count), n, tile0);
+    return ScanTube{T.n_keys, generic(T.cell_count), generic(T.cell_off), generic(T.blk_sum), generic(T.ctr),
+                    generic(T.sc), a.f32 ? sort_low_keys(T.c) : -1, generic(T.total_lo)};
 }
 
-// Exclusive scan of every tube's key counts in three phases over blocks of
-// SORT_SCAN_TILE keys (a block never spans two tubes): block totals, a scan of
-// each tube's block totals (one block per tube), then the offsets.
-__global__ __launch_bounds__(256) void k_bscan_totals(BSortArgs a)
+__global__ __launch_bounds__(SORT_BLOCK) void k_bscan_totals(BSortArgs a)
 {
-    __shared__ long long s_wave[4];
     const int t = a.scan_map[blockIdx.x];
-    const TubeDev &T = a.tubes[t];
-    const int64_t lb = blockIdx.x - a.scan_pref[t];
-    const int64_t base = lb * SORT_SCAN_TILE + (int64_t)threadIdx.x * 4;
-    long long s = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s += base + k < T.n_keys ? T.cell_count[base + k] : 0;
-    const long long inc = block_scan_incl(s, s_wave);
-    if (threadIdx.x == 255) T.blk_sum[lb] = inc;
+    if (a.scan_pref[t + 1] - a.scan_pref[t] <= SCAN_DIRECT) return;
+    scan_totals(scan_tube(a, a.tubes[t]), blockIdx.x - a.scan_pref[t]);
 }
 
-__global__ __launch_bounds__(256) void k_bscan_blocks(BSortArgs a)
+__global__ __launch_bounds__(SORT_BLOCK) void k_bscan_blocks(BSortArgs a)
 {
-    __shared__ long long s_wave[4];
-    __shared__ long long s_carry;
-    const TubeDev &T = a.tubes[blockIdx.x];
-    const int64_t nb = a.scan_pref[blockIdx.x + 1] - a.scan_pref[blockIdx.x];
-    if (threadIdx.x == 0) s_carry = 0;
-    __syncthreads();
-    for (int64_t b0 = 0; b0 < nb; b0 += 256) {
-        const int64_t i = b0 + threadIdx.x;
-        const long long v = i < nb ? T.blk_sum[i] : 0;
-        const long long inc = block_scan_incl(v, s_wave);
-        const long long carry = s_carry;
-        if (i < nb) T.blk_sum[i] = carry + inc - v;
-        __syncthreads();
-        if (threadIdx.x == 255) s_carry = carry + inc;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) T.ctr->n_alive = s_carry;
+    const int64_t nblk = a.scan_pref[blockIdx.x + 1] - a.scan_pref[blockIdx.x];
+    if (nblk > SCAN_SUMS) scan_blocks(scan_tube(a, a.tubes[blockIdx.x]), nblk);
 }
 
-__global__ __launch_bounds__(256) void k_bscan_apply(BSortArgs a)
+__global__ __launch_bounds__(SORT_BLOCK) void k_bscan_apply(BSortArgs a)
 {
-    __shared__ long long s_wave[4];
     const int t = a.scan_map[blockIdx.x];
-    const TubeDev &T = a.tubes[t];
-    const int64_t lb = blockIdx.x - a.scan_pref[t];
-    const int64_t base = lb * SORT_SCAN_TILE + (int64_t)threadIdx.x * 4;
-    long long v[4];
-    long long s = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[k] = base + k < T.n_keys ? T.cell_count[base + k] : 0;
-        s += v[k];
-    }
-    const long long inc = block_scan_incl(s, s_wave);
-    long long run = T.blk_sum[lb] + inc - s;
-    const int64_t klo = a.f32 ? sort_low_keys(T.c) : -1;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (base + k < T.n_keys) {
-            T.cell_off[base + k] = run;
-            if (base + k == klo) *T.total_lo = run;   // slots of the low destination stream
-        }
-        run += v[k];
-    }
+    const int64_t b0 = a.scan_pref[t];
+    scan_apply(scan_tube(a, a.tubes[t]), blockIdx.x - b0, a.scan_pref[t + 1] - b0);
 }
 
 __global__ __launch_bounds__(SORT_BLOCK) void k_bsort_scatter(BSortArgs a)
@@ -253,9 +201,12 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_bsort_scatter(BSortArgs a)
     const int t = a.chunk_map[it];
     const TubeDev &T = a.tubes[t];
     const Consts c = T.c;
+    const int64_t b0 = a.chunk_pref[t];
+    sort_finish(generic(T.cell_count), T.n_keys, generic(T.ctr), a.f32 ? generic(T.total_lo) : nullptr, it - b0,
+                a.chunk_pref[t + 1] - b0);
     bool hi;
     int64_t tile0, n;
-    if (!sort_item(it - a.chunk_pref[t], a.f32 != 0, generic(T.ctr), hi, tile0, n)) return;
+    if (!sort_item(it - b0, a.f32 != 0, generic(T.sc), hi, tile0, n)) return;
     unsigned long long *off = (unsigned long long *)generic(T.cell_off);
     if (a.f32) {
         const int64_t tlo = *T.total_lo;
@@ -267,21 +218,6 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_bsort_scatter(BSortArgs a)
         scatter_tile_f64(c, generic(T.x[a.src]), generic(T.u[a.src]), generic(T.x[a.dst]), generic(T.u[a.dst]), off,
                          n, tile0);
     }
-}
-
-__global__ __launch_bounds__(64) void k_bsort_finish(BSortArgs a)
-{
-    const int t = blockIdx.x * 64 + threadIdx.x;
-    if (t >= a.n_tubes) return;
-    const TubeDev &T = a.tubes[t];
-    if (a.f32) {
-        const long long lo = *T.total_lo;
-        T.ctr->n_slots_hi = T.ctr->n_alive - lo;
-        T.ctr->n_slots = lo;
-    } else {
-        T.ctr->n_slots = T.ctr->n_alive;
-    }
-    T.ctr->n_removed = 0;
 }
 
 // ------------------------------------------------------------------------
@@ -380,18 +316,21 @@ static BSortArgs bsort_args(pic_handle *h)
                      1 - t0->pbuf};
 }
 
-// Zero every tube's key counts before the step that accumulates them.
+// Zero every tube's key counts, if a sort has not left them so, before the step that
+// accumulates them.
 hipError_t launch_batch_clear(pic_handle *h)
 {
+    if (h->counts_clear) return hipSuccess;
     if (h->batch_scan_blocks <= 0 || h->batch_scan_blocks > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_bsort_clear, dim3((unsigned)h->batch_scan_blocks), dim3(256), 0, h->stream, bsort_args(h));
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    h->counts_clear = e == hipSuccess;
+    return e;
 }
 
 // nsteps steps of every tube: the work-list, push and field kernels per step.
-// With hist_last, the key counts are cleared first and the last step's push
-// counts the sort keys of its survivors (the sort that follows skips its
-// histogram).  With ev (timed runs), four events per step are recorded around
+// With hist_last, the last step's push counts the sort keys of its survivors for
+// the sort that follows.  With ev (timed runs), four events per step are recorded around
 // the work-list, push and field kernels (ev[4s] .. ev[4s + 3], created by the
 // caller).
 hipError_t launch_batch_steps(pic_handle *h, int nsteps, bool hist_last, hipEvent_t *ev)
@@ -403,10 +342,6 @@ hipError_t launch_batch_steps(pic_handle *h, int nsteps, bool hist_last, hipEven
         return hipErrorInvalidValue;
     pic_handle *t0 = h->tubes[0];
     const unsigned pgrid = (unsigned)h->batch_push_items, fgrid = (unsigned)h->batch_field_items;
-    if (hist_last) {
-        const hipError_t e = launch_batch_clear(h);
-        if (e != hipSuccess) return e;
-    }
     const bool f32 = t0->p.precision == PIC_FP32_BULK;
     for (int s = 0; s < nsteps; ++s) {
         BatchArgs a{h->d_tubes, (int)h->tubes.size(), h->d_live_pref, h->d_live_counts, h->d_push_map,
@@ -429,25 +364,26 @@ hipError_t launch_batch_steps(pic_handle *h, int nsteps, bool hist_last, hipEven
     return hipSuccess;
 }
 
-// The batched sort; hist_ready: the key counts were taken by the last push.
-hipError_t launch_batch_sort(pic_handle *h, bool hist_ready)
+// The batched sort; the key counts were taken by the last push.
+hipError_t launch_batch_sort(pic_handle *h)
 {
-    const int nt = (int)h->tubes.size();
     const BSortArgs a = bsort_args(h);
     if (h->batch_scan_blocks <= 0 || h->batch_scan_blocks > 0x7fffffff) return hipErrorInvalidValue;
     const unsigned sb = (unsigned)h->batch_scan_blocks;
     if (h->batch_sort_items <= 0 || h->batch_sort_items > 0x7fffffff) return hipErrorInvalidValue;
-    const unsigned g = (unsigned)h->batch_sort_items;   // one block per sort item
-    if (!hist_ready) {
-        hipLaunchKernelGGL(k_bsort_clear, dim3(sb), dim3(256), 0, h->stream, a);
-        hipLaunchKernelGGL(k_bsort_hist, dim3(g), dim3(SORT_BLOCK), 0, h->stream, a);
+    int64_t most = 0;   // scan blocks of the largest tube
+    for (const pic_handle *t : h->tubes) {
+        const int64_t nb = scan_blocks_of(sort_key_count(t->c, t->p.precision == PIC_FP32_BULK));
+        if (nb > most) most = nb;
     }
-    hipLaunchKernelGGL(k_bscan_totals, dim3(sb), dim3(256), 0, h->stream, a);
-    hipLaunchKernelGGL(k_bscan_blocks, dim3(nt), dim3(256), 0, h->stream, a);
-    hipLaunchKernelGGL(k_bscan_apply, dim3(sb), dim3(256), 0, h->stream, a);
-    hipLaunchKernelGGL(k_bsort_scatter, dim3(g), dim3(SORT_BLOCK), 0, h->stream, a);
-    hipLaunchKernelGGL(k_bsort_finish, dim3((nt + 63) / 64), dim3(64), 0, h->stream, a);
-    return hipGetLastError();
+    if (most > SCAN_DIRECT) hipLaunchKernelGGL(k_bscan_totals, dim3(sb), dim3(SORT_BLOCK), 0, h->stream, a);
+    if (most > SCAN_SUMS)
+        hipLaunchKernelGGL(k_bscan_blocks, dim3((unsigned)h->tubes.size()), dim3(SORT_BLOCK), 0, h->stream, a);
+    hipLaunchKernelGGL(k_bscan_apply, dim3(sb), dim3(SORT_BLOCK), 0, h->stream, a);
+    hipLaunchKernelGGL(k_bsort_scatter, dim3((unsigned)h->batch_sort_items), dim3(SORT_BLOCK), 0, h->stream, a);
+    const hipError_t e = hipGetLastError();
+    h->counts_clear = e == hipSuccess;
+    return e;
 }
 
 }  // namespace pcpic

@@ -39,48 +39,22 @@ __global__ __launch_bounds__(BLOCK) void k_push_f32(Consts c, Push32Args a, int 
 // sort and append for the two streams
 // ------------------------------------------------------------------------
 
-// Histogram for the sort (sort_key_f32: the destination stream's key range),
-// one block per tile of either stream (sort_item).
-__global__ __launch_bounds__(SORT_BLOCK) void k_hist32(Consts c, Streams s, const DevCounters *ctr, double u_hi,
-                                                       unsigned long long *count)
-{
-    bool hi;
-    int64_t tile0, n;
-    if (!sort_item(blockIdx.x, true, ctr, hi, tile0, n)) return;
-    hist_tile(c, true, hi, nullptr, s, u_hi, count, n, tile0);
-}
-
 // Scatter into the other buffer, one block per tile of either stream; tlo is
 // the destination low stream's slot count (the offset of the first high key).
-__global__ __launch_bounds__(SORT_BLOCK) void k_scatter32(Consts c, Streams src, Streams dst, const DevCounters *ctr,
-                                                          double u_hi, unsigned long long *off,
-                                                          const long long *total_lo)
+__global__ __launch_bounds__(SORT_BLOCK) void k_scatter32(Consts c, Streams src, Streams dst, DevCounters *ctr,
+                                                          const StepScratch *sc, double u_hi,
+                                                          unsigned long long *off, const long long *total_lo,
+                                                          long long *count, int64_t n_keys)
 {
+    sort_finish(count, n_keys, ctr, total_lo, blockIdx.x, gridDim.x);
     bool hi;
     int64_t tile0, n;
-    if (!sort_item(blockIdx.x, true, ctr, hi, tile0, n)) return;
+    if (!sort_item(blockIdx.x, true, sc, hi, tile0, n)) return;
     const int64_t tlo = *total_lo;
     if (hi)
         scatter_tile_f32<true>(c, src, dst, u_hi, tlo, off, n, tile0);
     else
         scatter_tile_f32<false>(c, src, dst, u_hi, tlo, off, n, tile0);
-}
-
-// Low-destination total = exclusive offset of the first high key; copied before
-// the scatter's atomics advance that offset.
-__global__ void k_copy_total(const long long *src, long long *dst)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *src;
-}
-
-__global__ void k_sort32_finish(DevCounters *ctr, const long long *total_lo)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        const long long lo = *total_lo;
-        ctr->n_slots_hi = ctr->n_alive - lo;
-        ctr->n_slots = lo;
-        ctr->n_removed = 0;
-    }
 }
 
 // Staged particles (x in cell units, u) -> validity count.
@@ -240,23 +214,12 @@ hipError_t launch_push_f32(pic_handle *h)
 // Blocks of a pass over both streams in tiles of SORT_TILE slots (sort_item).
 static unsigned sort_items32(pic_handle *h) { return (unsigned)((h->c.cap + SORT_TILE - 1) / SORT_TILE + 1); }
 
-hipError_t launch_sort32_hist(pic_handle *h)
-{
-    hipLaunchKernelGGL(k_hist32, dim3(sort_items32(h)), dim3(SORT_BLOCK), 0, h->stream, h->c, streams_of(h, h->pbuf),
-                       h->ws.ctr, h->u_hi, (unsigned long long *)h->ws.cell_count);
-    return hipGetLastError();
-}
-
-hipError_t launch_sort32_scatter(pic_handle *h)
+hipError_t launch_sort32_scatter(pic_handle *h, int64_t n_keys)
 {
     const int src = h->pbuf, dst = 1 - h->pbuf;
-    hipLaunchKernelGGL(k_copy_total, dim3(1), dim3(64), 0, h->stream, (const long long *)(h->ws.cell_off + sort_low_keys(h->c)),
-                       h->ws.total_lo);
     hipLaunchKernelGGL(k_scatter32, dim3(sort_items32(h)), dim3(SORT_BLOCK), 0, h->stream, h->c, streams_of(h, src),
-                       streams_of(h, dst), h->ws.ctr, h->u_hi, (unsigned long long *)h->ws.cell_off,
-                       (const long long *)h->ws.total_lo);
-    hipLaunchKernelGGL(k_sort32_finish, dim3(1), dim3(64), 0, h->stream, h->ws.ctr,
-                       (const long long *)(h->ws.total_lo));
+                       streams_of(h, dst), h->ws.ctr, h->ws.sc, h->u_hi, (unsigned long long *)h->ws.cell_off,
+                       (const long long *)h->ws.total_lo, h->ws.cell_count, n_keys);
     return hipGetLastError();
 }
 

@@ -138,9 +138,9 @@ __host__ __device__ inline int64_t sort_key_count(const Consts &c, bool f32)
     return (f32 ? 2 * (c.N + 1) : c.N) << c.sub;
 }
 __host__ __device__ inline int64_t sort_low_keys(const Consts &c) { return (c.N + 1) << c.sub; }
-constexpr int SORT_SCAN_TILE = 1024;   // keys per block of the three-phase scan
-constexpr int SORT_BLOCK = 256;        // threads per block of the scatter and histogram passes
-constexpr int SORT_PPT = 4;            // consecutive slots per thread in those passes
+constexpr int SORT_SCAN_TILE = 1024;   // keys per block of the scan
+constexpr int SORT_BLOCK = 256;        // threads per block of the scan and scatter passes
+constexpr int SORT_PPT = 4;            // consecutive slots per thread of the scatter
 constexpr int SORT_TILE = SORT_BLOCK * SORT_PPT;
 __device__ inline int64_t sort_key_f64(const Consts &c, double x)
 {
@@ -176,10 +176,12 @@ struct DevCounters {
 
 // State of a run of fused steps (k_step.hip) between its kernels: the slot count
 // that the pushes of a step take (two words in turn) and the node-0 tallies of
-// three steps in turn (all zero between runs).
+// three steps in turn (all zero between runs).  sort_n: the slots of the two streams
+// that a sort reads, kept for its scatter, which sets the counters to the new ones.
 struct StepScratch {
     int64_t n[2];
     unsigned long long w0[3];
+    int64_t sort_n[2];
 };
 
 struct Workspace {
@@ -337,6 +339,7 @@ struct pic_handle {
     int fbuf = 0;       // field buffer holding E^n, B^{n-1/2}
     int jbuf = 0;       // current buffer that the next step deposits into (0 or 1, clear)
     int jlast = 1;      // current buffer of the last step
+    bool counts_clear = false;   // the sort key counts (a batch: every tube's) are zero
     int64_t step = 0;   // steps enqueued
     int push_block = 64;
     int push_ppt = 2;
@@ -441,10 +444,8 @@ struct PackArgs {
     int n;
 };
 hipError_t launch_pack(pic_handle *h, const PackArgs &a, void *dst);
-hipError_t launch_sort32_hist(pic_handle *h);
-hipError_t launch_sort32_scatter(pic_handle *h);
+hipError_t launch_sort32_scatter(pic_handle *h, int64_t n_keys);
 hipError_t launch_append_staged(pic_handle *h, int64_t n, bool check_only);
-hipError_t launch_scan(pic_handle *h, int64_t n_keys);
 hipError_t launch_batch_steps(pic_handle *h, int nsteps, bool hist_last, hipEvent_t *ev = nullptr);
 hipError_t launch_copy_slots(pic_handle *h, const double *X, const double *U, double *Xc, double *Uc);
 hipError_t launch_zero_f64(pic_handle *h, double *p, int64_t n);
@@ -452,7 +453,7 @@ hipError_t launch_adj_step(pic_handle *h, const AdjStepPtrs &s);
 hipError_t launch_adj_finish(pic_handle *h, const double *lez, const double *ler, double *gphi, double *cp,
                              double *dp, double *g_rho, double *params);
 hipError_t launch_zero_i64(pic_handle *h, int64_t *p, int64_t n);
-hipError_t launch_batch_sort(pic_handle *h, bool hist_ready);
+hipError_t launch_batch_sort(pic_handle *h);
 hipError_t launch_batch_clear(pic_handle *h);
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t n16, hipStream_t stream);
 bool batch_shape_supported(pic_handle *h);
@@ -462,8 +463,8 @@ hipError_t launch_check_append(pic_handle *h, int64_t base, int64_t n);
 hipError_t launch_commit_append(pic_handle *h, int64_t n);
 hipError_t launch_kick(pic_handle *h);
 hipError_t launch_gauss(pic_handle *h);
-// Counting sort; hist_ready = the key counts were accumulated by the step before.
-hipError_t launch_sort(pic_handle *h, bool hist_ready);
+// Counting sort; the key counts were accumulated by the step before, and are zero afterwards.
+hipError_t launch_sort(pic_handle *h);
 hipError_t launch_clear_hist(pic_handle *h);
 
 // The lapse of PIC_GR_ALPHA: alpha^2 = 1 - r_g/r at height z, eta = r/R_* = 1 + z/R_*;

@@ -629,6 +629,7 @@ static pic_status tube_steps_direct(pic_handle *h, int64_t m)
 {
     const bool sort_after = h->p.sort_every > 0 && (h->step + m) % h->p.sort_every == 0;
     if (sort_after) HIP_OK(launch_clear_hist(h));
+    if (sort_after) h->counts_clear = false;   // until the sort has cleared them
     if (m > 1 && fused(h)) {
         HIP_OK(launch_run(h, m, sort_after));
     } else {
@@ -644,7 +645,7 @@ static pic_status tube_steps_direct(pic_handle *h, int64_t m)
         }
     }
     h->step += m;
-    if (sort_after) HIP_OK(launch_sort(h, true));
+    if (sort_after) HIP_OK(launch_sort(h));
     return PIC_OK;
 }
 
@@ -674,6 +675,7 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
     while (n_steps > 0) {
         if (S > 1 && h->use_graph && h->step % S == 0 && n_steps >= S) {
             const int key = h->fbuf | (h->jbuf << 1) | (h->pbuf << 2);
+            if (sorts) HIP_OK(launch_clear_hist(h));   // no part of the captured round
             if (!h->graph[key]) {
                 const int fb = h->fbuf, jb = h->jbuf, jl = h->jlast, pb = h->pbuf;
                 const int64_t st = h->step;
@@ -774,6 +776,7 @@ pic_status pic_step_timed(pic_handle *h, int64_t n_steps, pic_timing *out)
         hipEvent_t *e = &ev[(size_t)s * 4];
         const bool sort_after = h->p.sort_every > 0 && (h->step + 1) % h->p.sort_every == 0;
         if (sort_after && launch_clear_hist(h) != hipSuccess) { rc = fail(PIC_EDEVICE, "clear launch failed"); break; }
+        if (sort_after) h->counts_clear = false;
         h->hist_on = sort_after;
         const bool ok = hipEventRecord(e[0], h->stream) == hipSuccess && launch_push(h) == hipSuccess &&
                         hipEventRecord(e[1], h->stream) == hipSuccess && launch_field_inject(h) == hipSuccess &&
@@ -788,7 +791,7 @@ pic_status pic_step_timed(pic_handle *h, int64_t n_steps, pic_timing *out)
         h->jbuf ^= 1;
         h->step += 1;
         const bool sorted = sort_after;
-        if (sort_after && launch_sort(h, true) != hipSuccess) { rc = fail(PIC_EDEVICE, "sort launch failed"); break; }
+        if (sort_after && launch_sort(h) != hipSuccess) { rc = fail(PIC_EDEVICE, "sort launch failed"); break; }
         if (hipEventRecord(e[3], h->stream) != hipSuccess) { rc = fail(PIC_EDEVICE, "event record failed"); break; }
         slots_before[(size_t)s] = sorted ? -1 : 0;
     }
@@ -1632,12 +1635,12 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
         const bool run = h->batch_run_blocks > 0 && r > 1 && !ev;   // fused steps (timed runs measure push and field apart)
         const int key = t0->fbuf | (t0->jbuf << 1) | (t0->pbuf << 2);
         const bool round = to_sort && r == S && h->use_graph && !ev;
+        if (to_sort) HIP_OK(launch_batch_clear(h));
         if (round && !h->graph[key]) {
             hipGraph_t g = nullptr;
             if (hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-                hipError_t e1 = run ? launch_batch_clear(h) : launch_batch_steps(h, (int)r, true);
-                if (run && e1 == hipSuccess) e1 = launch_batch_run(h, r, true);
-                hipError_t e2 = launch_batch_sort(h, true);
+                hipError_t e1 = run ? launch_batch_run(h, r, true) : launch_batch_steps(h, (int)r, true);
+                hipError_t e2 = launch_batch_sort(h);
                 hipError_t e3 = hipStreamEndCapture(h->stream, &g);
                 if (e1 == hipSuccess && e2 == hipSuccess && e3 == hipSuccess && g &&
                     hipGraphInstantiate(&h->graph[key], g, nullptr, nullptr, 0) == hipSuccess) {
@@ -1662,14 +1665,14 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
                 e = &(*ev)[ev->size() - ne];
                 for (size_t k = 0; k < ne; ++k) HIP_OK(hipEventCreate(&e[k]));
             }
+            if (to_sort) h->counts_clear = false;   // until the sort has cleared them
             if (run) {
-                if (to_sort) HIP_OK(launch_batch_clear(h));
                 HIP_OK(launch_batch_run(h, r, to_sort));
             } else {
                 HIP_OK(launch_batch_steps(h, (int)r, to_sort, e));
             }
             if (e) HIP_OK(hipEventRecord(e[ne - 2], h->stream));
-            if (to_sort) HIP_OK(launch_batch_sort(h, true));
+            if (to_sort) HIP_OK(launch_batch_sort(h));
             if (e) HIP_OK(hipEventRecord(e[ne - 1], h->stream));
             if (tim) {
                 tim->push_launches += r;

@@ -1,5 +1,5 @@
-// sort_body.h -- per-tile bodies of the scatter pass of the cell sort, shared
-// by the single-tube kernels and the batched sort.
+// sort_body.h -- bodies of the scan and scatter passes of the cell sort, shared by
+// the single-tube kernels and the batched sort.
 //
 // A tile is SORT_TILE consecutive source slots, taken by a block of
 // SORT_BLOCK threads as SORT_PPT columns of SORT_BLOCK consecutive slots
@@ -55,18 +55,137 @@ __device__ __forceinline__ void hi_put_wide(const Streams &s, int64_t q, int cel
 // Destination stream of a particle: the high stream from |u| >= u_hi on.
 __device__ __forceinline__ bool goes_high(double u, double u_hi) { return fabs(u) >= u_hi; }
 
+// Exclusive scan of the key counts, one block of SORT_BLOCK threads per
+// SORT_SCAN_TILE keys.  What comes before a block's keys is summed by the block itself:
+// from the counts up to SCAN_DIRECT blocks (no other kernel), from block totals
+// (scan_totals) up to SCAN_SUMS blocks, and past that it is read from a scan of those
+// totals (scan_blocks).
+// Small sorts are bound by their launches: a round of two steps and a sort of an empty
+// tube took, with totals and their scan / totals / counts only, 24.6 / 23.0 / 21.1 us at
+// 2 blocks, 25.0 / 23.7 / 23.3 at 8, 25.4 / 24.1 / 25.7 at 16.  The sums of totals grow
+// with the square of the blocks: 247 (scanned) / 242 us at 2048, 956 / 940 at 8192.
+constexpr int64_t SCAN_DIRECT = 8;
+constexpr int64_t SCAN_SUMS = 8192;
+
+struct ScanTube {
+    int64_t n_keys;
+    const long long *count;
+    long long *off, *blk;
+    DevCounters *ctr;
+    StepScratch *sc;
+    int64_t klo;            // first key of the high stream (-1: one stream)
+    long long *total_lo;    // its offset
+};
+__host__ __device__ inline int64_t scan_blocks_of(int64_t n_keys) { return (n_keys + SORT_SCAN_TILE - 1) / SORT_SCAN_TILE; }
+
+__device__ __forceinline__ void scan_load(const long long *count, int64_t n, int64_t base, long long (&v)[4],
+                                          long long &s)
+{
+    static_assert(SORT_SCAN_TILE == 4 * SORT_BLOCK, "four keys per thread");
+    s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = base + k < n ? count[base + k] : 0;
+        s += v[k];
+    }
+}
+
+__device__ __forceinline__ void scan_totals(const ScanTube &t, int64_t lb)
+{
+    __shared__ long long s_wave[SORT_BLOCK / 64];
+    long long v[4], s;
+    scan_load(t.count, t.n_keys, lb * SORT_SCAN_TILE + (int64_t)threadIdx.x * 4, v, s);
+    const long long inc = block_scan_incl(s, s_wave);
+    if (threadIdx.x == SORT_BLOCK - 1) t.blk[lb] = inc;
+}
+
+// Exclusive scan of the block totals (one block, sequential chunks).
+__device__ __forceinline__ void scan_blocks(const ScanTube &t, int64_t nblk)
+{
+    __shared__ long long s_wave[SORT_BLOCK / 64];
+    __shared__ long long s_carry;
+    if (threadIdx.x == 0) s_carry = 0;
+    __syncthreads();
+    for (int64_t b0 = 0; b0 < nblk; b0 += SORT_BLOCK) {
+        const int64_t i = b0 + threadIdx.x;
+        const long long v = i < nblk ? t.blk[i] : 0;
+        const long long inc = block_scan_incl(v, s_wave);
+        const long long carry = s_carry;
+        if (i < nblk) t.blk[i] = carry + inc - v;
+        __syncthreads();
+        if (threadIdx.x == SORT_BLOCK - 1) s_carry = carry + inc;
+        __syncthreads();
+    }
+}
+
+// Offsets of the keys of block lb of nblk; the last block sets the live count, the
+// first keeps the source slot counts for the scatter.
+__device__ __forceinline__ void scan_apply(const ScanTube &t, int64_t lb, int64_t nblk)
+{
+    __shared__ long long s_wave[SORT_BLOCK / 64];
+    const int64_t base = lb * SORT_SCAN_TILE + (int64_t)threadIdx.x * 4;
+    long long v[4], s;
+    scan_load(t.count, t.n_keys, base, v, s);
+    long long run = 0;
+    if (nblk > SCAN_SUMS) {
+        run = t.blk[lb];
+    } else if (lb > 0) {
+        const bool direct = nblk <= SCAN_DIRECT;
+        const long long *p = direct ? t.count : t.blk;
+        const int64_t n = direct ? lb * SORT_SCAN_TILE : lb;
+        long long q = 0;
+#pragma unroll 4
+        for (int64_t i = threadIdx.x; i < n; i += SORT_BLOCK) q += p[i];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+        if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = q;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < SORT_BLOCK / 64; ++k) run += s_wave[k];
+        __syncthreads();
+    }
+    run += block_scan_incl(s, s_wave) - s;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (base + k < t.n_keys) {
+            t.off[base + k] = run;
+            if (base + k == t.klo) *t.total_lo = run;
+        }
+        run += v[k];
+    }
+    if (lb == nblk - 1 && threadIdx.x == SORT_BLOCK - 1) t.ctr->n_alive = run;
+    if (lb == 0 && threadIdx.x == 0) {
+        t.sc->sort_n[0] = t.ctr->n_slots;
+        t.sc->sort_n[1] = t.ctr->n_slots_hi;
+    }
+}
+
+// The scatter's blocks also clear the key counts, for the next step that accumulates
+// them, and its first sets the slot counts of the sorted streams.
+__device__ __forceinline__ void sort_finish(long long *count, int64_t n_keys, DevCounters *ctr,
+                                            const long long *total_lo, int64_t blk, int64_t nblk)
+{
+    for (int64_t i = blk * SORT_BLOCK + threadIdx.x; i < n_keys; i += nblk * SORT_BLOCK) count[i] = 0;
+    if (blk == 0 && threadIdx.x == 0) {
+        const int64_t n = ctr->n_alive, lo = total_lo ? *total_lo : n;
+        ctr->n_slots = lo;
+        ctr->n_slots_hi = n - lo;
+        ctr->n_removed = 0;
+    }
+}
+
 // Item k of a pass over a tube's slots in tiles of SORT_TILE: FP64 has one
 // stream; in FP32-bulk mode the low stream's tiles come first, then the high
 // stream's.  Returns false for an item past the slots (so ceil(capacity /
 // SORT_TILE) items, plus one in FP32-bulk mode, cover any split).
-__device__ __forceinline__ bool sort_item(int64_t k, bool f32, const DevCounters *ctr, bool &hi, int64_t &tile0,
+__device__ __forceinline__ bool sort_item(int64_t k, bool f32, const StepScratch *sc, bool &hi, int64_t &tile0,
                                           int64_t &n)
 {
-    const int64_t n_lo = ctr->n_slots;
+    const int64_t n_lo = sc->sort_n[0];
     const int64_t items_lo = (n_lo + SORT_TILE - 1) / SORT_TILE;
     hi = f32 && k >= items_lo;
     tile0 = (hi ? k - items_lo : k) * SORT_TILE;
-    n = hi ? ctr->n_slots_hi : n_lo;
+    n = hi ? sc->sort_n[1] : n_lo;
     return tile0 < n;
 }
 
@@ -172,38 +291,6 @@ __device__ __forceinline__ void scatter_tile_f32(const Consts &c, const Streams 
                 dst.UL[d] = (float)u[k];
             }
         }
-    }
-}
-
-// Sort-key counts of the slots [tile0, tile0 + SORT_TILE) of one stream (as
-// the scatter keys them), one atomic per run of equal keys in a wave.
-__device__ __forceinline__ void hist_tile(const Consts &c, bool f32, bool hi, const double *X, const Streams &s,
-                                          double u_hi, unsigned long long *count, int64_t n, int64_t tile0)
-{
-#pragma unroll 1
-    for (int q = 0; q < SORT_PPT; ++q) {
-        const int64_t p = tile0 + (int64_t)q * SORT_BLOCK + threadIdx.x;
-        bool live = false;
-        int64_t key = 0;
-        if (p < n) {
-            if (f32) {
-                float off = 0.0f;
-                const int cell = hi ? hi_slot(s, p, off) : s.CL[p];
-                if (cell >= 0) {
-                    const double u = hi ? s.UH[p] : (double)s.UL[p];
-                    live = true;
-                    key = sort_key_f32(c, cell, hi ? off : s.OL[p], goes_high(u, u_hi));
-                }
-            } else {
-                const double x = X[p];
-                if (x >= 0.0) {
-                    live = true;
-                    key = sort_key_f64(c, x);
-                }
-            }
-        }
-        const WaveRun r = wave_runs(key, live);
-        if (live && r.is_head) atomicAdd(count + key, (unsigned long long)(r.end - (int)__lane_id()));
     }
 }
 
