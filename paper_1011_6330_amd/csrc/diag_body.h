@@ -104,8 +104,8 @@ __device__ __forceinline__ void add_nodes(NodeWindow &s, unsigned long long *w, 
 
 // A wave's profile accumulator.  The partial sums are whole numbers in doubles:
 // a lane adds at most 2^21 gammas below 2^31 and their fractions of at most 2^32
-// units between two flushes (take_ok), so every sum is exact; larger gammas go
-// to the window one by one.
+// units between two flushes, so every sum is exact; larger gammas go to the window
+// one by one.
 struct ProfAcc {
     int bin = -1;                 // current bin (wave-uniform), -1: none
     int c = 0;

@@ -228,16 +228,24 @@ __global__ __launch_bounds__(MOM_BLOCK) void k_moments(Consts c, int nb, const d
     }
 }
 
-// Clears and accumulates the profile (nb > 0) into p and the node weights
-// (w_out non-null); clear_gauss also clears the Gauss maximum.
-hipError_t launch_moments(pic_handle *h, int nb, const ProfPtrs &p, int64_t *w_out, bool clear_gauss)
+hipError_t launch_clear_bins(pic_handle *h, int n, const ProfPtrs &p)
+{
+    hipLaunchKernelGGL(k_moments_clear, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, h->stream, n, p, (int64_t)0,
+                       nullptr, nullptr);
+    return hipGetLastError();
+}
+
+// Clears (the bins unless bins_clear) and accumulates the profile (nb > 0) into p and
+// the node weights (w_out non-null); clear_gauss also clears the Gauss maximum.
+hipError_t launch_moments(pic_handle *h, int nb, const ProfPtrs &p, int64_t *w_out, bool clear_gauss, bool bins_clear)
 {
     const Consts &c = h->c;
     const Workspace &w = h->ws;
-    const int64_t nw = w_out ? c.N + 1 : 0, m = nw > nb ? nw : (nb > 0 ? nb : 1);
+    const int64_t nw = w_out ? c.N + 1 : 0, nc = bins_clear ? 0 : nb, m = nw > nc ? nw : (nc > 0 ? nc : 1);
     unsigned long long *wo = (unsigned long long *)w_out;
-    hipLaunchKernelGGL(k_moments_clear, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, h->stream, nb, p, nw, wo,
-                       clear_gauss ? w.ctr : nullptr);
+    if (nc > 0 || nw > 0 || clear_gauss)
+        hipLaunchKernelGGL(k_moments_clear, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, h->stream, (int)nc, p, nw,
+                           wo, clear_gauss ? w.ctr : nullptr);
     if (nb <= 0 && !w_out) return hipGetLastError();
     // eight blocks per CU, fewer when the capacity does not give each MOM_MIN slots
     const int64_t most = (int64_t)h->n_cu * 8, fit = (c.cap + MOM_MIN - 1) / MOM_MIN;
@@ -282,6 +290,10 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs a, unsigned long long *ds
     for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2; i < g.words; i += (int64_t)gridDim.x * 512) {
         if (i + 2 <= g.words) *(l2 *)(dst + g.at + i) = *(const l2 *)(g.src + i);
         else dst[g.at + i] = g.src[i];
+        if (g.reset) {
+            g.src[i] = g.value;
+            if (i + 2 <= g.words) g.src[i + 1] = g.value;
+        }
     }
 }
 

@@ -339,6 +339,7 @@ struct pic_handle {
     int fbuf = 0;       // field buffer holding E^n, B^{n-1/2}
     int jbuf = 0;       // current buffer that the next step deposits into (0 or 1, clear)
     int jlast = 1;      // current buffer of the last step
+    bool bins_clear = false;     // every profile bin of the workspace is clear
     bool counts_clear = false;   // the sort key counts (a batch: every tube's) are zero
     int64_t step = 0;   // steps enqueued
     int push_block = 64;
@@ -428,21 +429,25 @@ struct ProfPtrs {
     long long *hi;
     long long *mn, *mx;
 };
-// The profile accumulated into the bins p (nb > 0) and the node weights into w_out
-// (non-null), both cleared first; clear_gauss also clears the Gauss maximum.
-hipError_t launch_moments(pic_handle *h, int nb, const ProfPtrs &p, int64_t *w_out, bool clear_gauss);
-// The bins copied out in the caller's layout.
-hipError_t launch_profile_finish(pic_handle *h, int nb, const ProfPtrs &p, int64_t *count, uint64_t *sum_lo,
-                                 int64_t *sum_hi, double *vmin, double *vmax);
 // Gather of several device arrays (16-byte aligned) into one host-visible buffer.
 struct PackSeg {
-    const unsigned long long *src;
+    unsigned long long *src;
     int64_t at, words;      // destination (even) and length in 8-byte words
+    int reset;              // the words are set to `value` once they are read
+    unsigned long long value;
 };
 struct PackArgs {
     PackSeg seg[13];
     int n;
 };
+// The profile accumulated into the bins p (nb > 0) and the node weights into w_out
+// (non-null), both cleared first (the bins unless bins_clear); clear_gauss also clears the Gauss maximum.
+hipError_t launch_moments(pic_handle *h, int nb, const ProfPtrs &p, int64_t *w_out, bool clear_gauss,
+                          bool bins_clear = false);
+hipError_t launch_clear_bins(pic_handle *h, int n, const ProfPtrs &p);
+// The bins copied out in the caller's layout.
+hipError_t launch_profile_finish(pic_handle *h, int nb, const ProfPtrs &p, int64_t *count, uint64_t *sum_lo,
+                                 int64_t *sum_hi, double *vmin, double *vmax);
 hipError_t launch_pack(pic_handle *h, const PackArgs &a, void *dst);
 hipError_t launch_sort32_scatter(pic_handle *h, int64_t n_keys);
 hipError_t launch_append_staged(pic_handle *h, int64_t n, bool check_only);

@@ -906,10 +906,6 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
     const int64_t N = h->c.N;
     const Workspace &w = h->ws;
     const bool gauss = want_gauss || out->gauss;
-    if (nb > 0 || gauss || out->weights)
-        HIP_OK(launch_moments(h, nb, ProfPtrs{w.pcount, w.plo, w.phi128, w.pmin, w.pmax},
-                              gauss || out->weights ? w.w : nullptr, gauss));
-    if (gauss) HIP_OK(launch_gauss(h));
     const int f = h->fbuf;
     std::vector<double> gtmp;                 // the residual, for its L2 norm, where the caller does not take it
     double *gdst = out->gauss;
@@ -925,16 +921,18 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
     // fits; the rest (and everything, where no buffer is to be had) array by array
     struct Want {
         void *dst;
-        const void *src;
+        void *src;
         size_t bytes;
+        bool bins;              // profile bins, of this clear value
+        long long clear;
     };
     const size_t nbytes = (size_t)nb * 8;
     const Want all[13] = {{&ctr, w.ctr, sizeof ctr},
-                          {cnt, w.pcount, nbytes},
-                          {lo, w.plo, nbytes},
-                          {hi, w.phi128, nbytes},
-                          {mn, w.pmin, nbytes},
-                          {mx, w.pmax, nbytes},
+                          {cnt, w.pcount, nbytes, true, 0},
+                          {lo, w.plo, nbytes, true, 0},
+                          {hi, w.phi128, nbytes, true, 0},
+                          {mn, w.pmin, nbytes, true, ordered_bits(INFINITY)},
+                          {mx, w.pmax, nbytes, true, ordered_bits(-INFINITY)},
                           {out->ez, w.ez[f], (size_t)N * 8},
                           {out->er, w.er[f], (size_t)(N + 1) * 8},
                           {out->b_phi, w.b[f], (size_t)N * 8},
@@ -949,7 +947,8 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
         if (!a.dst || a.bytes == 0) continue;
         const size_t sz = (a.bytes + 15) & ~(size_t)15;
         if (total + sz > PINNED_MAX) continue;
-        pk.seg[pk.n] = PackSeg{(const unsigned long long *)a.src, (int64_t)(total / 8), (int64_t)(a.bytes / 8)};
+        pk.seg[pk.n] = PackSeg{(unsigned long long *)a.src, (int64_t)(total / 8), (int64_t)(a.bytes / 8), a.bins ? 1 : 0,
+                                (unsigned long long)a.clear};
         packed[pk.n++] = a;
         total += sz;
     }
@@ -957,7 +956,23 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
     // and 120 us to give back, a tube that is read once would lose by it
     Pinned st(total, h->stream, (h->parent ? h->parent : h)->reads.fetch_add(1) > 0);
     st.idle = false;
+    const bool weights = gauss || out->weights;
+    const ProfPtrs bins{w.pcount, w.plo, w.phi128, w.pmin, w.pmax};
+    // the packing kernel leaves the bins clear for the next read-out
+    int packed_bins = 0;
+    for (int k = 0; k < pk.n; ++k) packed_bins += pk.seg[k].reset;
+    const bool leaves = st.b.p && packed_bins == 5;
+    bool clear = h->bins_clear;
+    h->bins_clear = clear && nb == 0;
+    if (!clear && leaves) {
+        HIP_OK(launch_clear_bins(h, effective_bins(h->p), bins));
+        clear = true;
+    }
+    if (nb > 0 || weights)
+        HIP_OK(launch_moments(h, nb, bins, weights ? w.w : nullptr, gauss, clear));
+    if (gauss) HIP_OK(launch_gauss(h));
     if (st.b.p) HIP_OK(launch_pack(h, pk, st.b.p));
+    if (leaves) h->bins_clear = true;
     int at = 0;
     for (const Want &a : all) {
         if (!a.dst || a.bytes == 0) continue;

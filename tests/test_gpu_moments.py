@@ -81,3 +81,24 @@ def test_repeated_readouts_equal_the_first(N):
             assert np.array_equal(d[k], v), k
     other.close()
     t.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_bins_are_clear_for_each_readout(precision):
+    """Read-outs of any number of bins after one another (each leaves the bins clear),
+    with steps, weights and fields between them."""
+    from paper_1011_6330_amd import Tube
+    N, n = 900, 3000
+    cfg = dict(synth.preset("c2"), n_cells=N, q_over_m=-1e-9, ppc=4.0, capacity=n + 100, sort_every=4,
+               precision=precision, gamma_fp64=20.0, max_bins=1000, flags=3)
+    t = Tube(synth.tube_params(cfg))
+    t.inject(*synth.random_particles(N, n, seed=1))
+    for nb, more in ((64, {}), (64, {}), (1000, {}), (1, dict(weights=True)), (0, {}), (37, dict(fields=False)), (999, {}),
+                     (0, dict(gauss=True)), (64, dict(fields=False)), (1000, dict(gauss=True))):
+        d = t.diagnostics(n_bins=nb, **more)
+        if nb:
+            exp = _expected(*t.read_particles(), N, nb, 32)
+            for k, v in zip(("prof_count", "prof_sum_lo", "prof_sum_hi", "prof_min", "prof_max"), exp):
+                assert np.array_equal(d[k], v), (nb, k)
+        t.step(3)
+    t.close()
