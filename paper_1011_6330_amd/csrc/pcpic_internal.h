@@ -321,6 +321,7 @@ struct AdjRecord {
     int64_t step_end = 0;       // the tube's step count after the forward
     int64_t mut = 0;            // the tube's change count after the forward
     int jb_final = 0, jl_final = 1;   // current buffers (next, last) after the forward
+    int64_t held[2] = {-1, -1}; // segment whose states each set of the tape's slots holds (-1: none)
 };
 
 // Buffers after a captured round.

@@ -1820,14 +1820,54 @@ pic_status adjoint_supported(pic_handle *h)
     return PIC_OK;
 }
 
+// States of a segment in the tape: step k of segment ck, whose slots k >= 1 lie in set q.
+struct SegSlots {
+    const Tape &t;
+    int64_t ck;
+    int q;
+    double *x(int64_t k) const { return k == 0 ? t.ck_x[ck] : t.sg_x[q][(size_t)k]; }
+    double *u(int64_t k) const { return k == 0 ? t.ck_u[ck] : t.sg_u[q][(size_t)k]; }
+    double *ez(int64_t k) const { return k == 0 ? t.ck_ez[ck] : t.sg_ez[q][(size_t)k]; }
+    double *er(int64_t k) const { return k == 0 ? t.ck_er[ck] : t.sg_er[q][(size_t)k]; }
+    double *b(int64_t k) const { return k == 0 ? t.ck_b[ck] : t.sg_b[q][(size_t)k]; }
+};
+
+// The set of segment slots that segment ck uses.
+int set_of(const Tape &t, int64_t ck) { return t.nsets == 2 ? (int)(ck & 1) : 0; }
+
+// m steps of a tube out of place, from the state in the segment's checkpoint: step k
+// leaves its state in slot k, the last in the tube's own arrays.
+hipError_t launch_run_recorded(pic_handle *h, const SegSlots &g, int64_t m, int64_t *rec)
+{
+    const Workspace &w = h->ws;
+    const int b = h->pbuf, f = h->fbuf ^ (int)(m & 1);
+    hipError_t e = hipSuccess;
+    for (int64_t s = 1; s <= m + 1 && e == hipSuccess; ++s) {
+        const int64_t o = s > 1 ? s - 2 : 0, n = s > 1 ? s - 1 : 0;
+        const bool end = n == m;
+        RunPtrs p{g.ez(o), g.er(o), g.b(o), end ? w.ez[f] : g.ez(n), end ? w.er[f] : g.er(n), end ? w.b[f] : g.b(n)};
+        p.X = end ? w.x[b] : g.x(s - 1);
+        p.U = end ? w.u[b] : g.u(s - 1);
+        if (!end) {
+            p.Xo = s == m ? w.x[b] : g.x(s);
+            p.Uo = s == m ? w.u[b] : g.u(s);
+        }
+        e = end ? launch_run_end(h, m, p, false, rec + s - 1) : launch_run_step(h, s, p, false, rec + s - 1);
+    }
+    h->fbuf = f;
+    return e;
+}
+
 // The checkpointed forward of n_steps steps (the same steps as pic_step),
-// recorded in the tape and in h->adj for the reverse sweep.
+// recorded in the tape and in h->adj for the reverse sweep.  The last segments, as
+// many as the tape has sets of slots, keep the states that the sweep starts with.
 pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, size_t tape_bytes, pic_adjoint_out *out)
 {
     Tape t = carve_tape(h, T, K, (uint8_t *)d_tape);
     Workspace &w = h->ws;
     const int64_t N = h->c.N;
     h->adj.valid = false;
+    h->adj.held[0] = h->adj.held[1] = -1;
     hipEvent_t ev[2] = {};
     for (auto &e : ev) HIP_OK(hipEventCreate(&e));
     auto done = [&](pic_status r) {
@@ -1854,7 +1894,12 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
             FWD_OK(hipMemcpyAsync(t.ck_ctr[ck], w.ctr, sizeof(DevCounters), hipMemcpyDeviceToDevice, h->stream));
         }
         // a fused run of the segment's steps, whose kernels note the slot counts
-        FWD_OK(launch_run(h, m, false, t.nslots + st));
+        if (ck >= t.nck - t.nsets) {
+            FWD_OK(launch_run_recorded(h, SegSlots{t, ck, set_of(t, ck)}, m, t.nslots + st));
+            h->adj.held[set_of(t, ck)] = ck;
+        } else {
+            FWD_OK(launch_run(h, m, false, t.nslots + st));
+        }
         h->step += m;
     }
     // keep what the recompute overwrites: counters and the last step's current
@@ -1890,12 +1935,12 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
     return done(PIC_OK);
 }
 
-// The reverse sweep of the recorded forward: each segment recomputed from its
-// checkpoint (on a second stream, one segment ahead), three kernels per
-// reversed step, the transposed Poisson solve; gradients scaled by dloss.
+// The reverse sweep of the recorded forward: each segment whose states the tape does
+// not hold (any more) recomputed from its checkpoint (on a second stream, one segment
+// ahead), two kernels per reversed step, the transposed Poisson solve; gradients scaled by dloss.
 pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
 {
-    const AdjRecord &r = h->adj;
+    AdjRecord &r = h->adj;
     Tape t = carve_tape(h, r.T, r.K, (uint8_t *)r.tape);
     Workspace &w = h->ws;
     const int64_t N = h->c.N, T = r.T, K = r.K, n_pre = r.n_pre, nex = r.n_exit;
@@ -1947,15 +1992,14 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
         const hipError_t e_ = (expr);                                                                \
         if (e_ != hipSuccess) return fail_rev(fail(PIC_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_))); \
     } while (0)
-    REV_OK(hipStreamCreateWithFlags(&rec_s, hipStreamNonBlocking));
     for (auto &e : sev) REV_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     REV_OK(hipEventRecord(sev[0], main_s));
-    REV_OK(hipStreamWaitEvent(rec_s, sev[0], 0));
     // recompute steps s0 .. s0+m-1 of segment ck out of place on rec_s: slot k of
     // its set holds the state before step s0+k
     auto recompute = [&](int64_t ck) -> hipError_t {
-        const int q = t.nsets == 2 ? (int)(ck & 1) : 0;
+        const SegSlots g{t, ck, set_of(t, ck)};
         const int64_t s0 = ck * K, m = (T - s0) < K ? (T - s0) : K;
+        r.held[g.q] = -1;
         h->stream = rec_s;
         hipError_t e = hipMemcpyAsync(w.ctr, t.ck_ctr[ck], sizeof(DevCounters), hipMemcpyDeviceToDevice, rec_s);
         if (e == hipSuccess) e = launch_zero_i64(h, w.j[0], N);
@@ -1964,42 +2008,48 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
         // s-1 to slot s and makes the field update from slot s-2 to slot s-1
         h->jbuf = 0;
         h->jlast = 1;
-        auto X = [&](int64_t k) { return k == 0 ? t.ck_x[ck] : t.sg_x[q][(size_t)k]; };
-        auto U = [&](int64_t k) { return k == 0 ? t.ck_u[ck] : t.sg_u[q][(size_t)k]; };
-        auto EZ = [&](int64_t k) { return k == 0 ? t.ck_ez[ck] : t.sg_ez[q][(size_t)k]; };
-        auto ER = [&](int64_t k) { return k == 0 ? t.ck_er[ck] : t.sg_er[q][(size_t)k]; };
-        auto B = [&](int64_t k) { return k == 0 ? t.ck_b[ck] : t.sg_b[q][(size_t)k]; };
         for (int64_t s = 1; m > 1 && s <= m && e == hipSuccess; ++s) {
             const int64_t o = s > 1 ? s - 2 : 0, n = s > 1 ? s - 1 : 0;
-            RunPtrs p{EZ(o), ER(o), B(o), EZ(n), ER(n), B(n), X(s - 1), U(s - 1), nullptr, nullptr};
+            RunPtrs p{g.ez(o), g.er(o), g.b(o), g.ez(n), g.er(n), g.b(n), g.x(s - 1), g.u(s - 1), nullptr, nullptr};
             if (s < m) {
-                p.Xo = X(s);
-                p.Uo = U(s);
+                p.Xo = g.x(s);
+                p.Uo = g.u(s);
                 e = launch_run_step(h, s, p, false, nullptr);
             } else {
                 e = launch_run_end(h, m - 1, p, false, nullptr);
             }
         }
         h->stream = main_s;
-        if (e == hipSuccess) e = hipEventRecord(sev[1 + q], rec_s);
+        if (e == hipSuccess) e = hipEventRecord(sev[1 + g.q], rec_s);
+        if (e == hipSuccess) r.held[g.q] = ck;
         return e;
     };
-    REV_OK(recompute(t.nck - 1));
+    bool waits[2] = {false, false};               // the set's states come from a recompute of this sweep
+    auto ensure = [&](int64_t ck) -> hipError_t {
+        const int q = set_of(t, ck);
+        if (r.held[q] == ck) return hipSuccess;
+        hipError_t e = hipSuccess;
+        if (!rec_s) {
+            e = hipStreamCreateWithFlags(&rec_s, hipStreamNonBlocking);
+            if (e == hipSuccess) e = hipStreamWaitEvent(rec_s, sev[0], 0);
+        }
+        // the set was last read by the sweep of segment ck + 2
+        if (e == hipSuccess && ck + 2 <= t.nck - 1) e = hipStreamWaitEvent(rec_s, sev[3 + q], 0);
+        waits[q] = true;
+        return e == hipSuccess ? recompute(ck) : e;
+    };
+    REV_OK(ensure(t.nck - 1));
     int64_t rev = 0;                              // reverse steps done (their parity picks the scale words)
     for (int64_t ck = t.nck - 1; ck >= 0; --ck) {
-        const int q = t.nsets == 2 ? (int)(ck & 1) : 0;
+        const SegSlots g{t, ck, set_of(t, ck)};
+        const int q = g.q;
         const int64_t s0 = ck * K, m = (T - s0) < K ? (T - s0) : K;
-        REV_OK(hipStreamWaitEvent(main_s, sev[1 + q], 0));
-        if (ck >= 1) {
-            // the other set was last read by the sweep of segment ck+1
-            if (ck + 1 <= t.nck - 1) REV_OK(hipStreamWaitEvent(rec_s, sev[3 + (q ^ 1)], 0));
-            REV_OK(recompute(ck - 1));
-        }
+        if (waits[q]) REV_OK(hipStreamWaitEvent(main_s, sev[1 + q], 0));
+        if (ck >= 1) REV_OK(ensure(ck - 1));
         for (int64_t k = m - 1; k >= 0; --k, ++rev) {
             const int64_t st = s0 + k;
             const int pp = (int)(rev & 1);
-            AdjStepPtrs a{k == 0 ? t.ck_x[ck] : t.sg_x[q][(size_t)k], k == 0 ? t.ck_u[ck] : t.sg_u[q][(size_t)k],
-                          k == 0 ? t.ck_ez[ck] : t.sg_ez[q][(size_t)k], t.nslots + st, t.nslots + st + 1, n_pre, nex,
+            AdjStepPtrs a{g.x(k), g.u(k), g.ez(k), t.nslots + st, t.nslots + st + 1, n_pre, nex,
                           t.lx, t.lu, t.lez, t.ler[pp], t.ler[pp ^ 1], t.lb, t.lbp[pp], t.lbp[pp ^ 1], t.lk_lo,
                           t.lk_hi, t.scale, (int)(rev % 3)};
             REV_OK(launch_adj_step(h, a));
