@@ -82,8 +82,8 @@ constexpr int HI_GROUP = 1 << HI_GROUP_LOG2;
 // Steps per captured round of a tube that never sorts (even: the field and
 // current buffers end a round in the parity they started it in).
 constexpr int64_t GRAPH_ROUND = 32;
-// Capacity up to which a tube (all tubes of a batch together) takes fused steps
-// (k_step.hip has the times on both sides of it); an adjoint run always does, as it
+// Expected slots (run_slots) up to which a tube (all tubes of a batch together) takes
+// fused steps (k_step.hip has the times on both sides of it); an adjoint run always does, as it
 // also saves a kernel per step there that notes the slot count.
 constexpr int64_t FUSE_SLOTS = (int64_t)1 << 22;
 
@@ -418,6 +418,7 @@ hipError_t launch_run(pic_handle *h, int64_t m, bool hist_last, int64_t *rec = n
 // The same for a batch; blocks of one of its tubes in a run's kernels.
 hipError_t launch_batch_run(pic_handle *h, int64_t m, bool hist_last);
 int64_t run_blocks(const pic_params &p);
+int64_t run_slots(const pic_params &p);
 // Current buffers of a run that starts with jb clear: step s (from 1) adds to
 // run_j(jb, s); after m steps run_j(jb, m) holds the last current and run_next(jb, m)
 // is clear.

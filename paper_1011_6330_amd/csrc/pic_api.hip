@@ -620,7 +620,7 @@ static pic_status batch_status(pic_handle *h);
 static void free_batch_graphs(pic_handle *h);
 
 // Small tubes take their steps in fused runs (k_step.hip).
-static bool fused(const pic_handle *h) { return h->c.cap <= FUSE_SLOTS && !(h->c.flags & PIC_GR_ALPHA); }
+static bool fused(const pic_handle *h) { return run_slots(h->p) <= FUSE_SLOTS && !(h->c.flags & PIC_GR_ALPHA); }
 
 // m steps of a single tube, launched directly, of which only the last may be
 // followed by a sort (its push counts the sort keys): fused, or step by step push
@@ -1411,7 +1411,7 @@ static BatchMapSizes batch_map_sizes(const pic_params *tubes, int n)
         m.chunk += (p.capacity + SORT_TILE - 1) / SORT_TILE + (f32 ? 1 : 0);
         const int64_t keys = (f32 ? 2 * (p.n_cells + 1) : p.n_cells) << sort_sub_log2(p);
         m.scan += (keys + SORT_SCAN_TILE - 1) / SORT_SCAN_TILE;
-        slots += p.capacity;
+        slots += run_slots(p);
     }
     if (slots <= FUSE_SLOTS)
         for (int t = 0; t < n; ++t) m.run += run_blocks(tubes[t]);

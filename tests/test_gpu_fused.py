@@ -36,6 +36,7 @@ CASES = {
     "dense_sorted": dict(cfg=dict(n_cells=700, ppc=60.0, sort_every=8), n=40000),
     "returning": dict(cfg=dict(q_over_m=+30.0), n=500),
     "clipped": dict(cfg=dict(capacity=600), n=100),
+    "roomy": dict(cfg=dict(n_cells=2000, capacity=5 << 20), n=40000),   # more slots than twice the expected ones
     "frozen": dict(cfg=dict(flags=2), n=500),
     "no_injection": dict(cfg=dict(flags=1), n=500),
 }
