@@ -26,7 +26,7 @@ struct Consts {
     int32_t P;        // fixed-point fraction bits
     uint32_t flags;   // PIC_* flags
     int32_t sub;      // log2 of the sort key's bins per cell
-    int32_t gr_fast;  // PIC_GR_ALPHA: the lapse constants lie where the push's short division and square root apply
+    int32_t gr_fast;  // PIC_GR_ALPHA: the lapse constants lie where the push's short division and square root apply (2: and cells are small)
     int64_t oneP;     // 2^P
     double twoP;      // 2^P as a double
     double dz;        // L / N
@@ -53,6 +53,7 @@ struct Consts {
     double rho_amp, kappa, r_star, length;
     double gr_s;      // PIC_RHO_GR: (3/2) theta_* tan(i) cos(varphi)
     double gr_g;      // PIC_RHO_GR or PIC_GR_ALPHA: r_g / R_*
+    double gr_rr;     // 1 / r_star
     double gr_cg;     // PIC_GR_ALPHA: dt (r_g/R_*) / (2 R_*); dt alpha alpha' = gr_cg / eta^2
 };
 

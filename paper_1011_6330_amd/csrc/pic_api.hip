@@ -251,7 +251,11 @@ Consts make_consts(const pic_params &p, const double *knots)
         // division's scaling steps do nothing (push_common.h, nr_div)
         auto num_ok = [](double v) { return v == 0.0 || (fabs(v) >= 0x1p-600 && fabs(v) <= 0x1p+400); };
         auto den_ok = [](double v) { return fabs(v) >= 0x1p-300 && fabs(v) <= 0x1p+300; };
+        // (den_ok bounds every height too); 2: half a cell is at most 2^-10 R_*, so the
+        // reciprocal at the start of the step leads to the one at its midpoint
         c.gr_fast = (num_ok(c.gr_g) && num_ok(c.gr_cg) && den_ok(p.r_star) && den_ok(c.dz)) ? 1 : 0;
+        if (c.gr_fast && c.dz <= 0x1p-9 * p.r_star) c.gr_fast = 2;
+        c.gr_rr = 1.0 / p.r_star;
     }
     c.rho0 = rho_node(c, knots, 0);
     c.qm = p.macro_charge != 0.0 ? p.macro_charge : (c.rho0 * c.dz) / p.ppc;

@@ -142,16 +142,16 @@ __device__ __forceinline__ void push_one_f64(const Consts &c, const PushArgs &a,
         // gs_sqrt: the same bits) when every live lane's operands allow them
         const double zx = x * c.dz;
         const bool fast = c.gr_fast && __all(!live || nr_num_ok(zx));
-        double eta, a2, al, kg, g0, gh;
+        double eta, re = 0.0, a2, al, kg, g0, gh;
         double t0 = u * u;
         t0 = 1.0 + t0;
         if (fast) {
-            const double rr = nr_recip(c.r_star);
-            eta = 1.0 + nr_div(zx, c.r_star, rr);
-            a2 = 1.0 - nr_div(c.gr_g, eta, nr_recip(eta));
+            eta = 1.0 + nr_div(zx, c.r_star, c.gr_rr);
+            re = nr_recip(eta);
+            a2 = 1.0 - nr_div(c.gr_g, eta, re);
             al = gs_sqrt(a2);
             const double e2 = eta * eta;
-            kg = nr_div(c.gr_cg, e2, nr_recip(e2));
+            kg = nr_div(c.gr_cg, e2, nr_recip_last(e2, re * re));
             g0 = gs_sqrt(t0);
         } else {
             eta = 1.0 + zx / c.r_star;
@@ -172,8 +172,8 @@ __device__ __forceinline__ void push_one_f64(const Consts &c, const PushArgs &a,
         const double zh = xh * c.dz;
         double a2h;
         if (fast && __all(!live || nr_num_ok(zh))) {
-            const double eh = 1.0 + nr_div(zh, c.r_star, nr_recip(c.r_star));
-            a2h = 1.0 - nr_div(c.gr_g, eh, nr_recip(eh));
+            const double eh = 1.0 + nr_div(zh, c.r_star, c.gr_rr);
+            a2h = 1.0 - nr_div(c.gr_g, eh, c.gr_fast == 2 ? nr_recip_near(eh, re) : nr_recip(eh));
         } else {
             a2h = gr_alpha2(c, zh);
         }

@@ -173,14 +173,15 @@ struct DepAcc {
 // gamma = sqrt(tt) and v = u / gamma for tt = 1 + u^2, both correctly rounded.
 // Square root: Goldschmidt iteration from the hardware reciprocal square root
 // estimate y (g = tt y, h = y/2, one joint correction, then two residual
-// corrections g += (tt - g^2) h).  Quotient: Newton-Raphson reciprocal from the
-// hardware estimate (two steps), q = u r, and one residual correction
-// q += (u - gamma q) r (Markstein).  These are the operations, in order, that
-// the general correctly rounded double-precision square root and division
-// perform when their range scaling does not apply, which holds for tt >= 1 and
-// 2^-400 <= |u| <= 2^400; outside that range (u = 0 included) the general
-// routines are called.  Skipping the scaling and special-case steps saves
-// about a dozen instructions per particle.
+// corrections g += (tt - g^2) h).  Quotient: a Newton step on the reciprocal 2 h
+// that the square root has at hand, q = u r, and one residual correction
+// q += (u - gamma q) r (Markstein).  The square root's operations are, in order,
+// those of the general correctly rounded routine where its range scaling does not
+// apply, which holds for tt >= 1 and 2^-400 <= |u| <= 2^400; outside that range
+// (u = 0 included) the general routines are called.  Skipping the scaling and
+// special-case steps saves about a dozen instructions per particle, and h in place
+// of the hardware's reciprocal estimate (to 2^-23, as the estimate that h starts
+// from, and a quarter of the rate) and of its first Newton step saves three more.
 __device__ __forceinline__ void gamma_velocity(double u, double tt, double &gam, double &v)
 {
     const double y = __builtin_amdgcn_rsq(tt);
@@ -192,11 +193,7 @@ __device__ __forceinline__ void gamma_velocity(double u, double tt, double &gam,
     g = fma(d, h, g);
     d = fma(-g, g, tt);
     g = fma(d, h, g);
-    double rc = __builtin_amdgcn_rcp(g);
-    double e = fma(-g, rc, 1.0);
-    rc = fma(rc, e, rc);
-    e = fma(-g, rc, 1.0);
-    rc = fma(rc, e, rc);
+    const double rc = nr_recip_last(g, h + h);
     const double q = u * rc;
     const double rem = fma(-g, q, u);
     gam = g;

@@ -4,6 +4,9 @@
 //   nr_recip(d): the hardware reciprocal estimate and two Newton steps;
 //   nr_div(n, d, nr_recip(d)) = n / d for |d| in [2^-300, 2^300] and n = 0 or
 //     |n| in [2^-600, 2^400] (no operand scaling, no denormal quotient);
+//   nr_recip_last(d, r), nr_recip_near(d, r): nr_recip(d)'s accuracy from a reciprocal
+//     known to 2^-26 or to 2^-10 of its value instead of the hardware estimate (one
+//     Newton step, or a cubic step and one);
 //   gs_sqrt(t) = sqrt(t) for finite t >= 2^-767 (Goldschmidt from the hardware
 //     reciprocal square root estimate, then two residual corrections).
 #pragma once
@@ -20,6 +23,17 @@ __device__ __forceinline__ double nr_recip(double d)
     r = fma(r, e, r);
     e = fma(-d, r, 1.0);
     return fma(r, e, r);
+}
+__device__ __forceinline__ double nr_recip_last(double d, double r)
+{
+    const double e = fma(-d, r, 1.0);
+    return fma(r, e, r);
+}
+__device__ __forceinline__ double nr_recip_near(double d, double r)
+{
+    const double e = fma(-d, r, 1.0);
+    const double s = fma(e, e, e);
+    return nr_recip_last(d, fma(r, s, r));
 }
 __device__ __forceinline__ double nr_div(double n, double d, double r)
 {
@@ -39,7 +53,8 @@ __device__ __forceinline__ double gs_sqrt(double t)
     d = fma(-g, g, t);
     return fma(d, h, g);
 }
-// a dividend nr_div takes: 0 or a magnitude within [2^-600, 2^400]
-__device__ __forceinline__ bool nr_num_ok(double n) { return n == 0.0 || (fabs(n) >= 0x1p-600 && fabs(n) <= 0x1p+400); }
+// a dividend nr_div takes that is known to lie below 2^400 (or is not a number): 0 or a
+// magnitude from 2^-600 on
+__device__ __forceinline__ bool nr_num_ok(double n) { return n == 0.0 || fabs(n) >= 0x1p-600; }
 
 }  // namespace pcpic
