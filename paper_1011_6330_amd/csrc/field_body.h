@@ -117,6 +117,15 @@ __device__ __forceinline__ void push_injected(const Consts &c, const FieldArgs &
     }
 }
 
+// alpha at height z (a node's or a face's), with the bits of gr_alpha_node and
+// gr_alpha_face: their division and square root in short form where gr_fast allows.
+__device__ __forceinline__ double gr_alpha_at(const Consts &c, double z)
+{
+    if (!c.gr_fast) return sqrt(gr_alpha2(c, z));
+    const double eta = 1.0 + nr_div(z, c.r_star, c.gr_rr);
+    return gs_sqrt(1.0 - nr_div(c.gr_g, eta, nr_recip(eta)));
+}
+
 // Leap-frog update of eq. (3) at face i (the update of face N-1 also owns node N):
 //   B_{i+1/2}  <- B - [ (dt/dz)(E_r,i+1 - E_r,i) + (dt/R) E_z,i+1/2 ]
 //   E_r,i      <- E_r,i - (dt/dz)(B_{i+1/2} - B_{i-1/2}),  i = 1..N-1 (E_r,0 unchanged, = 0)
@@ -126,6 +135,7 @@ __device__ __forceinline__ void push_injected(const Consts &c, const FieldArgs &
 // expression instead of being exchanged.  PIC_GR_ALPHA puts the lapse on each
 // term (alpha B/R, alpha d(alpha E_r)/dz, alpha d(alpha B)/dz, alpha E_z/R, with
 // alpha at faces and nodes as pcpic.h states).  Returns the new E_z.
+template <int GR>
 __device__ __forceinline__ double field_cell(const Consts &c, const FieldArgs &a, int64_t i)
 {
     const int64_t N = c.N;
@@ -136,13 +146,15 @@ __device__ __forceinline__ double field_cell(const Consts &c, const FieldArgs &a
         a.bn[i] = a.bo[i];
         a.ern[i] = a.ero[i];
         if (i == N - 1) a.ern[N] = a.ero[N];
-    } else if (c.flags & PIC_GR_ALPHA) {
+    } else if (GR) {
         // the same update with the lapse on each term (alpha at faces af, nodes an)
-        const double af = gr_alpha_face(c, i), an0 = gr_alpha_node(c, i), an1 = gr_alpha_node(c, i + 1);
+        const double af = gr_alpha_at(c, ((double)i + 0.5) * c.dz), an0 = gr_alpha_at(c, (double)i * c.dz),
+                     an1 = gr_alpha_at(c, (double)(i + 1) * c.dz);
         const double bi = a.bo[i] - (c.dtdz * (af * (an1 * a.ero[i + 1] - an0 * a.ero[i])) + c.dtR * (af * a.ezo[i]));
         a.bn[i] = bi;
         if (i >= 1) {
-            const double afm = gr_alpha_face(c, i - 1), anm = gr_alpha_node(c, i - 1);
+            const double afm = gr_alpha_at(c, ((double)(i - 1) + 0.5) * c.dz),
+                         anm = gr_alpha_at(c, (double)(i - 1) * c.dz);
             const double bm = a.bo[i - 1] - (c.dtdz * (afm * (an0 * a.ero[i] - anm * a.ero[i - 1])) +
                                              c.dtR * (afm * a.ezo[i - 1]));
             a.ern[i] = a.ero[i] - c.dtdz * (an0 * (af * bi - afm * bm));
@@ -262,21 +274,26 @@ __device__ __forceinline__ double field_wave_pairs(const Consts &c, const FieldA
 // field_wave_pairs where the flat update applies to the wave's whole span, else
 // FIELD_CPT consecutive faces per thread with field_cell face by face; the
 // block of tile 0 then applies the SCLF rule.  Called by all threads of a block
-// of bs threads (a multiple of 64).
+// of bs threads (a multiple of 64).  GR (PIC_GR_ALPHA): one face per thread, since a face with the
+// lapse is five square roots and ten divisions, and four in a row (or side by side in
+// one thread) are a chain that few waves have nothing to hide behind: 20,011 cells
+// took 6.8 us, and take 5.0.
+template <int GR = 0>
 __device__ __forceinline__ void field_tile(const Consts &c, const FieldArgs &a, int64_t tile, int bs)
 {
     __shared__ double s_ez0;
     __shared__ long long s_base, s_n;
     const int64_t N = c.N;
-    const int64_t i0 = (tile * bs + threadIdx.x) * FIELD_CPT;
+    constexpr int CPT = GR ? 1 : FIELD_CPT;
+    const int64_t i0 = (tile * bs + threadIdx.x) * CPT;
     const int64_t w0 = (tile * bs + (threadIdx.x & ~63)) * FIELD_CPT;   // the wave's first face (uniform)
     static_assert(FIELD_CPT == 4, "a wave takes 256 faces");
-    if (!(c.flags & (PIC_FREEZE_FIELDS | PIC_GR_ALPHA)) && w0 + 256 <= N) {
+    if (!GR && !(c.flags & PIC_FREEZE_FIELDS) && w0 + 256 <= N) {
         const double ez = field_wave_pairs(c, a, w0);
         if (w0 + 2 * (int)__lane_id() == 0) s_ez0 = ez;
     } else if (i0 < N) {
-        const double ez = field_cell(c, a, i0);
-        for (int k = 1; k < FIELD_CPT && i0 + k < N; ++k) field_cell(c, a, i0 + k);
+        const double ez = field_cell<GR>(c, a, i0);
+        for (int k = 1; k < CPT && i0 + k < N; ++k) field_cell<GR>(c, a, i0 + k);
         if (i0 == 0) s_ez0 = ez;
     }
     if (tile != 0) return;
@@ -293,7 +310,7 @@ __device__ __forceinline__ void field_tile(const Consts &c, const FieldArgs &a, 
         const int64_t slots_hi = __hip_atomic_load(&ctr->n_slots_hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const double t1 = c.qmP * (double)w0;
         double t2 = c.rho0 * c.hdz;
-        if (c.flags & PIC_GR_ALPHA) t2 = t2 / gr_alpha_node(c, 0);   // rho_GJ,0 / alpha_0 over the half cell
+        if (GR) t2 = t2 / gr_alpha_node(c, 0);   // rho_GJ,0 / alpha_0 over the half cell
         const double es = s_ez0 - c.fourpi * (t1 - t2);
         int64_t ninj = 0;
         const int64_t ks = ctr->step - a.sched_first;   // index of this step in a replayed schedule

@@ -151,9 +151,10 @@ __global__ __launch_bounds__(256) void k_fill_i64(int64_t *p, int64_t n, int64_t
     if (i < n) p[i] = v;
 }
 
+template <int GR>
 __global__ __launch_bounds__(256) void k_field_inject(Consts c, FieldArgs a)
 {
-    field_tile(c, a, blockIdx.x, 256);
+    field_tile<GR>(c, a, blockIdx.x, 256);
 }
 
 // FP32-bulk: the f32 kick array from E_z (after the caller overwrote the fields).
@@ -264,7 +265,10 @@ hipError_t launch_field_inject(pic_handle *h)
                 h->d_sched, h->sched_first, h->sched_n,
                 h->hist_on ? (unsigned long long *)w.cell_count : nullptr,
                 f32 && 0.0 >= h->u_hi ? sort_low_keys(c) : 0};
-    hipLaunchKernelGGL(k_field_inject, dim3(grid_for(c.N, 256 * FIELD_CPT)), dim3(256), 0, h->stream, c, a);
+    if (c.flags & PIC_GR_ALPHA)
+        hipLaunchKernelGGL((k_field_inject<1>), dim3(grid_for(c.N, 256)), dim3(256), 0, h->stream, c, a);
+    else
+        hipLaunchKernelGGL((k_field_inject<0>), dim3(grid_for(c.N, 256 * FIELD_CPT)), dim3(256), 0, h->stream, c, a);
     return hipGetLastError();
 }
 
