@@ -584,8 +584,10 @@ pic_status pic_inject(pic_handle *h, int64_t n, const double *x, const double *u
             return fail(PIC_EINVAL, "%lld particles outside [0, N) or not finite", (long long)ctr.bad_inputs);
         for (int64_t o = 0; o < n; o += ch) {
             const int64_t m = n - o < ch ? n - o : ch;
-            HIP_OK(hipMemcpyAsync(h->ws.stage_x, x + o, (size_t)m * 8, kind, h->stream));
-            HIP_OK(hipMemcpyAsync(h->ws.stage_u, u + o, (size_t)m * 8, kind, h->stream));
+            if (n > ch) {   // a single stage still holds what was validated
+                HIP_OK(hipMemcpyAsync(h->ws.stage_x, x + o, (size_t)m * 8, kind, h->stream));
+                HIP_OK(hipMemcpyAsync(h->ws.stage_u, u + o, (size_t)m * 8, kind, h->stream));
+            }
             HIP_OK(launch_append_staged(h, m, false));
         }
         if (h->step == 0) {
