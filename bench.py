@@ -312,13 +312,14 @@ def main():
         gcfg = dict(cfg, flags=int(cfg.get("flags", 0)) | GR_ALPHA, rg_over_rstar=0.4)
         g0, g1, gtim, gel, _ = run_tube(gcfg, x, u, 0, args.steps, args.warmup, push=push)
         gval = 0.5 * (g0["n_alive"] + g1["n_alive"]) * args.steps / gel
-        groof = roofline_of(B_FP64 * gtim["alive"], gtim, "k_push_f64<128, 2, 1, 1>")
+        gnt = bool(push and push[2])
+        groof = roofline_of(B_FP64 * gtim["alive"], gtim, f"k_push_f64<128, 2, {int(gnt)}, 1>")
         result["gr_alpha"] = {"value": gval, "unit": "particle-steps/s", "ms_per_step": gel / args.steps * 1e3,
                               "roofline": groof, "vs_flat": gval / value,
                               "workload": "the c2 tube with the lapse alpha (r_g/R_* = 0.4) in Maxwell's equations "
                                           "and the equation of motion (PIC_GR_ALPHA), FP64"}
         # the full-GR push is launched at 128 x 2 whatever the configured shape
-        busy = measured_traffic((128, 2, True), GR_SQ_FILE, PUSH_SOURCES, key="valu_busy_us")
+        busy = measured_traffic((128, 2, gnt), GR_SQ_FILE, PUSH_SOURCES, key="valu_busy_us")
         if busy is not None:
             result["gr_alpha"]["valu"] = {
                 "busy_us": busy, "frac_of_push": busy / groof["avg_launch_us"],

@@ -204,7 +204,7 @@ const char *pic_last_error(void);
 /* Device workspace bytes pic_init needs for these parameters, or 0 if the
  * parameters are invalid (then pic_last_error says why).  The workspace holds
  * two particle buffers of `capacity` slots (16 B each, FP64), the field arrays
- * twice (leap-frog ping-pong), the current, kick and Poisson arrays, the
+ * twice (leap-frog ping-pong), the current three times, the kick and Poisson arrays, the
  * counters and the sort and profile scratch. */
 size_t pic_workspace_bytes(const pic_params *p);
 
@@ -277,7 +277,9 @@ typedef struct pic_timing {
 
 /* pic_step(h, n_steps) with a HIP event recorded on the handle's stream around
  * every kernel group; synchronises at the end and fills *out.  Used to measure
- * per-kernel durations; the events add a little launch overhead.
+ * per-kernel durations; the events add a little launch overhead, and a tube or batch
+ * small enough for fused steps (one kernel for the push and the field update) takes
+ * separate kernels here.
  * Errors: as pic_step, plus PIC_EDEVICE for event failures. */
 pic_status pic_step_timed(pic_handle *h, int64_t n_steps, pic_timing *out);
 
@@ -302,7 +304,9 @@ pic_status pic_set_push_config(pic_handle *h, int32_t block, int32_t per_thread,
  *
  * A batch holds n_tubes tubes of any sizes (each tube's parameters as for
  * pic_init; all tubes share the precision and sort_every).  pic_step on the
- * batch handle advances every tube.  Each step is a push kernel and a field
+ * batch handle advances every tube.  A batch of up to 4.2 million expected slots takes
+ * one kernel per step (the field update of the step before and the push); in a larger
+ * one each step is a push kernel and a field
  * kernel over all tubes, over device lists of (tube, tile) work items, one
  * block per item.  No block waits for another;
  * the kernel boundary orders the phases.  Up to sort_every steps plus a batched

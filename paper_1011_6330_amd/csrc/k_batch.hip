@@ -1,15 +1,15 @@
 // k_batch.hip -- many independent tubes of uneven size stepped together.
 //
 // Each tube keeps the exact workspace layout of a single tube; a device table
-// of TubeDev descriptors points at them.  A step of the whole batch is two
-// kernels over a device work list, one block per item:
+// of TubeDev descriptors points at them.  A batch of up to FUSE_SLOTS expected slots
+// takes its steps in fused runs, one kernel per step (k_step.hip).  In a larger one a
+// step is a work list and two kernels over it, one block per item:
 //   push  -- items = particle tiles of every tube (both streams in FP32-bulk
 //            mode); the body is the single-tube push_tile_*;
 //   field -- items = cell tiles of every tube; the body is the single-tube
 //            field_tile, whose tile-0 block also injects.
-// The kernel boundary orders the two phases, so no block ever waits for
-// another and nothing depends on how many blocks are resident or on what else
-// shares the GPU.  A round of up to sort_every steps plus the batched cell sort
+// The kernel boundaries order the phases, so no block ever waits for another and
+// nothing depends on how many blocks are resident or on what else shares the GPU.  A round of up to sort_every steps plus the batched cell sort
 // is captured once in a HIP graph and replayed with a single launch.  A tube
 // therefore computes bit for bit what it computes when stepped alone.
 #include <math.h>

@@ -16,6 +16,12 @@
 // straight-line code with selects, so lanes that stay in their cell and lanes
 // that cross a face share one instruction stream; the rare boundary events
 // (exit, return, node-0 tally) are added by the lanes that have them.
+//
+// What bounds it: 4e7 particles move 1.28 GB per step, 192 us at the copy rate, and
+// take 209 (138 of vector instructions).  With the lapse (GR) the instructions do:
+// 440 per wave of 128 particles against 248, 6.1e6 particles 64.2 us with the general
+// reciprocals and 60.6 with those at hand, 38.6 of it issue, where their 195 MB stay
+// in the last-level cache.
 #include <math.h>
 
 #include "pcpic_internal.h"

@@ -5,6 +5,12 @@
 // key taking consecutive slots.  Every step of the method is per
 // particle or an integer reduction, so the order this produces (which varies
 // from run to run between waves of the same cell) never changes a result.
+//
+// Two kernels up to 8192 keys, three up to 8.4 million (sort_body.h); the scatter
+// also clears the counts and sets the slot counts.  A small sort is bound by its
+// launches (a tube of 1024 cells, 205 steps with a sort every 16: 1210 us with six
+// kernels per sort, 1138 with two), a large one by its scattered writes (2.5e8
+// particles 1.56 ms, 1.2 at the copy rate).
 #include <math.h>
 
 #include "pcpic_internal.h"
