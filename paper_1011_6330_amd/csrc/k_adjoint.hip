@@ -112,19 +112,18 @@ __device__ __forceinline__ void wave_add_runs_fixed(unsigned long long *lo, long
     if (want && (int)__lane_id() == r.end - 1 && s != 0.0) fixed_add(lo + key, hi + key, s, e);
 }
 
-__global__ __launch_bounds__(256) void k_copy_slots(const double *X, const double *U, double *Xc, double *Uc,
-                                                    const DevCounters *ctr)
+// Copies and clears of whole arrays in one launch, segment by grid row: what a segment
+// of the forward keeps, what a recompute starts from, the adjoints before the sweep.
+// One kernel per array (five, three and nine of them) cost 3 to 4 us each, mostly launch.
+__global__ __launch_bounds__(256) void k_copy_segs(CopySegs a, const DevCounters *ctr)
 {
-    const int64_t n = ctr->n_slots;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        Xc[i] = X[i];
-        Uc[i] = U[i];
+    typedef unsigned long long l2 __attribute__((ext_vector_type(2)));
+    const CopySeg g = a.seg[blockIdx.y];
+    const int64_t n = g.words >= 0 ? g.words : ctr->n_slots;
+    for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2; i < n; i += (int64_t)gridDim.x * 512) {
+        if (i + 2 <= n) *(l2 *)(g.dst + i) = g.src ? *(const l2 *)(g.src + i) : l2{0, 0};
+        else g.dst[i] = g.src ? g.src[i] : 0;
     }
-}
-
-__global__ __launch_bounds__(256) void k_fill_f64(double *p, int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.0;
 }
 
 // The quanta of a reverse step from the maxima of the adjoints it starts from
@@ -461,15 +460,16 @@ __global__ __launch_bounds__(256) void k_adj_params(Consts c, const double *knot
 
 static inline unsigned gridn(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-hipError_t launch_copy_slots(pic_handle *h, const double *X, const double *U, double *Xc, double *Uc)
+hipError_t launch_copy_segs(pic_handle *h, const CopySegs &a)
 {
-    hipLaunchKernelGGL(k_copy_slots, dim3(h->n_cu * 8), dim3(256), 0, h->stream, X, U, Xc, Uc, h->ws.ctr);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_f64(pic_handle *h, double *p, int64_t n)
-{
-    if (n > 0) hipLaunchKernelGGL(k_fill_f64, dim3(gridn(n) < 4096 ? gridn(n) : 4096), dim3(256), 0, h->stream, p, n);
+    int64_t most = 1;
+    for (int k = 0; k < a.n; ++k) {
+        const int64_t w = a.seg[k].words >= 0 ? a.seg[k].words : h->c.cap;
+        most = w > most ? w : most;
+    }
+    const int64_t blocks = (most + 511) / 512, cap = (int64_t)h->n_cu * 8;
+    hipLaunchKernelGGL(k_copy_segs, dim3((unsigned)(blocks < cap ? blocks : cap), (unsigned)a.n), dim3(256), 0, h->stream,
+                       a, h->ws.ctr);
     return hipGetLastError();
 }
 

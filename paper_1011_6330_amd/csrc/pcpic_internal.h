@@ -455,8 +455,22 @@ hipError_t launch_pack(pic_handle *h, const PackArgs &a, void *dst);
 hipError_t launch_sort32_scatter(pic_handle *h, int64_t n_keys);
 hipError_t launch_append_staged(pic_handle *h, int64_t n, bool check_only);
 hipError_t launch_batch_steps(pic_handle *h, int nsteps, bool hist_last, hipEvent_t *ev = nullptr);
-hipError_t launch_copy_slots(pic_handle *h, const double *X, const double *U, double *Xc, double *Uc);
-hipError_t launch_zero_f64(pic_handle *h, double *p, int64_t n);
+// Arrays (16-byte aligned) copied or cleared together: `words` 8-byte words of each, or
+// (words < 0) as many as the tube has slots.
+struct CopySeg {
+    unsigned long long *dst;
+    const unsigned long long *src;   // null: cleared
+    int64_t words;
+};
+struct CopySegs {
+    CopySeg seg[9];
+    int n;
+    void add(void *dst, const void *src, int64_t words)
+    {
+        seg[n++] = CopySeg{(unsigned long long *)dst, (const unsigned long long *)src, words};
+    }
+};
+hipError_t launch_copy_segs(pic_handle *h, const CopySegs &a);
 hipError_t launch_adj_step(pic_handle *h, const AdjStepPtrs &s);
 hipError_t launch_adj_finish(pic_handle *h, const double *lez, const double *ler, double *gphi, double *cp,
                              double *dp, double *g_rho, double *params);

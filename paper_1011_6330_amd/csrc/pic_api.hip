@@ -1826,6 +1826,9 @@ pic_status adjoint_supported(pic_handle *h)
     return PIC_OK;
 }
 
+constexpr int64_t CTR_WORDS = (int64_t)(sizeof(DevCounters) / 8);
+static_assert(sizeof(DevCounters) % 8 == 0 && sizeof(AdjScale) % 8 == 0, "copied in 8-byte words");
+
 // States of a segment in the tape: step k of segment ck, whose slots k >= 1 lie in set q.
 struct SegSlots {
     const Tape &t;
@@ -1893,11 +1896,14 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
         const int64_t ck = st / K, m = T - st < K ? T - st : K;
         {
             const int f = h->fbuf;
-            FWD_OK(launch_copy_slots(h, w.x[h->pbuf], w.u[h->pbuf], t.ck_x[ck], t.ck_u[ck]));
-            FWD_OK(hipMemcpyAsync(t.ck_ez[ck], w.ez[f], (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
-            FWD_OK(hipMemcpyAsync(t.ck_er[ck], w.er[f], (size_t)(N + 1) * 8, hipMemcpyDeviceToDevice, h->stream));
-            FWD_OK(hipMemcpyAsync(t.ck_b[ck], w.b[f], (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
-            FWD_OK(hipMemcpyAsync(t.ck_ctr[ck], w.ctr, sizeof(DevCounters), hipMemcpyDeviceToDevice, h->stream));
+            CopySegs g{};
+            g.add(t.ck_x[ck], w.x[h->pbuf], -1);
+            g.add(t.ck_u[ck], w.u[h->pbuf], -1);
+            g.add(t.ck_ez[ck], w.ez[f], N);
+            g.add(t.ck_er[ck], w.er[f], N + 1);
+            g.add(t.ck_b[ck], w.b[f], N);
+            g.add(t.ck_ctr[ck], w.ctr, CTR_WORDS);
+            FWD_OK(launch_copy_segs(h, g));
         }
         // a fused run of the segment's steps, whose kernels note the slot counts
         if (ck >= t.nck - t.nsets) {
@@ -1909,8 +1915,10 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
         h->step += m;
     }
     // keep what the recompute overwrites: counters and the last step's current
-    FWD_OK(hipMemcpyAsync(t.final_ctr, w.ctr, sizeof(DevCounters), hipMemcpyDeviceToDevice, h->stream));
-    FWD_OK(hipMemcpyAsync(t.final_jlast, w.j[h->jlast], (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
+    CopySegs keep{};
+    keep.add(t.final_ctr, w.ctr, CTR_WORDS);
+    keep.add(t.final_jlast, w.j[h->jlast], N);
+    FWD_OK(launch_copy_segs(h, keep));
     FWD_OK(hipEventRecord(ev[1], h->stream));
     DevCounters c1;
     s = read_counters(h, &c1);
@@ -1968,15 +1976,17 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
     // counts and owns the adjoint arrays), and events order each recompute
     // before its sweep and each set's reuse after its sweep.
     ADJ_OK(hipEventRecord(ev[0], h->stream));
-    ADJ_OK(launch_zero_f64(h, t.lx, t.cap));
-    ADJ_OK(launch_zero_f64(h, t.lu, t.cap));
-    ADJ_OK(launch_zero_f64(h, t.lez, N));
-    ADJ_OK(launch_zero_f64(h, t.ler[0], N + 1));
-    ADJ_OK(launch_zero_f64(h, t.lb, N));
-    ADJ_OK(launch_zero_f64(h, t.lbp[0], N));     // B adjoint of the last step: nothing depends on E^T yet
-    ADJ_OK(launch_zero_f64(h, (double *)t.lk_lo, N));
-    ADJ_OK(launch_zero_f64(h, (double *)t.lk_hi, N));
-    ADJ_OK(launch_zero_f64(h, (double *)t.scale, (int64_t)(sizeof(AdjScale) / 8)));
+    CopySegs zero{};
+    zero.add(t.lx, nullptr, -1);          // of the slots that the run ended with
+    zero.add(t.lu, nullptr, -1);
+    zero.add(t.lez, nullptr, N);
+    zero.add(t.ler[0], nullptr, N + 1);
+    zero.add(t.lb, nullptr, N);
+    zero.add(t.lbp[0], nullptr, N);       // B adjoint of the last step: nothing depends on E^T yet
+    zero.add(t.lk_lo, nullptr, N);
+    zero.add(t.lk_hi, nullptr, N);
+    zero.add(t.scale, nullptr, (int64_t)(sizeof(AdjScale) / 8));
+    ADJ_OK(launch_copy_segs(h, zero));
     hipStream_t const main_s = h->stream;
     hipStream_t rec_s = nullptr;
     hipEvent_t sev[5] = {};                       // forward done; recompute done [2]; sweep done [2]
@@ -2007,9 +2017,11 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
         const int64_t s0 = ck * K, m = (T - s0) < K ? (T - s0) : K;
         r.held[g.q] = -1;
         h->stream = rec_s;
-        hipError_t e = hipMemcpyAsync(w.ctr, t.ck_ctr[ck], sizeof(DevCounters), hipMemcpyDeviceToDevice, rec_s);
-        if (e == hipSuccess) e = launch_zero_i64(h, w.j[0], N);
-        if (e == hipSuccess) e = launch_zero_i64(h, w.j[1], N);
+        CopySegs from{};
+        from.add(w.ctr, t.ck_ctr[ck], CTR_WORDS);
+        from.add(w.j[0], nullptr, N);
+        from.add(w.j[1], nullptr, N);
+        hipError_t e = launch_copy_segs(h, from);
         // a fused run of the segment's steps but the last: kernel s pushes from slot
         // s-1 to slot s and makes the field update from slot s-2 to slot s-1
         h->jbuf = 0;
@@ -2067,11 +2079,13 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
     ADJ_OK(launch_adj_finish(h, t.lez, t.ler[(int)(T & 1)], t.gphi, t.cp, t.dp, t.g_rho, t.params));
     ADJ_OK(hipEventRecord(ev[1], h->stream));
     // restore the end state the forward left
-    ADJ_OK(hipMemcpyAsync(w.ctr, t.final_ctr, sizeof(DevCounters), hipMemcpyDeviceToDevice, h->stream));
     h->jbuf = r.jb_final;
     h->jlast = r.jl_final;
-    ADJ_OK(launch_zero_i64(h, w.j[h->jbuf], N));
-    ADJ_OK(hipMemcpyAsync(w.j[h->jlast], t.final_jlast, (size_t)N * 8, hipMemcpyDeviceToDevice, h->stream));
+    CopySegs end{};
+    end.add(w.ctr, t.final_ctr, CTR_WORDS);
+    end.add(w.j[h->jbuf], nullptr, N);
+    end.add(w.j[h->jlast], t.final_jlast, N);
+    ADJ_OK(launch_copy_segs(h, end));
     // results
     std::vector<double> params((size_t)h->c.n_knots + 2);
     double grate = 0.0;
