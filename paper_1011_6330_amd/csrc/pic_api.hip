@@ -247,13 +247,17 @@ Consts make_consts(const pic_params &p, const double *knots)
     c.gr_g = (p.rho_kind == PIC_RHO_GR || (p.flags & PIC_GR_ALPHA)) ? p.rg_over_rstar : 0.0;
     c.gr_cg = ((0.5 * c.dt) * c.gr_g) / p.r_star;
     {
-        // the GR push's short forms need its fixed operands where the general
-        // division's scaling steps do nothing (push_common.h, nr_div)
+        // the short forms with the lapse need their operands where the general
+        // division's scaling steps do nothing (short_math.h, nr_div); den_ok bounds every
+        // height too, and the length keeps eta and eta^2, divisors themselves, in range.
+        // 2: half a cell is at most 2^-10 R_*, so the reciprocal at the start of the step
+        // leads to the one at its midpoint
         auto num_ok = [](double v) { return v == 0.0 || (fabs(v) >= 0x1p-600 && fabs(v) <= 0x1p+400); };
         auto den_ok = [](double v) { return fabs(v) >= 0x1p-300 && fabs(v) <= 0x1p+300; };
-        // (den_ok bounds every height too); 2: half a cell is at most 2^-10 R_*, so the
-        // reciprocal at the start of the step leads to the one at its midpoint
-        c.gr_fast = (num_ok(c.gr_g) && num_ok(c.gr_cg) && den_ok(p.r_star) && den_ok(c.dz)) ? 1 : 0;
+        c.gr_fast = (num_ok(c.gr_g) && num_ok(c.gr_cg) && den_ok(p.r_star) && den_ok(c.dz) &&
+                     p.length <= 0x1p+148 * p.r_star)
+                        ? 1
+                        : 0;
         if (c.gr_fast && c.dz <= 0x1p-9 * p.r_star) c.gr_fast = 2;
         c.gr_rr = 1.0 / p.r_star;
     }
