@@ -227,6 +227,9 @@ pic_status pic_inject(pic_handle *h, int64_t n, const double *x, const double *u
 /* Enqueue n_steps PIC cycles on the stream and return.  Each cycle: push and
  * charge-conserving deposit, boundary removal, leap-frog field update, SCLF
  * injection; every sort_every cycles a cell sort that drops removed particles.
+ * Kernels only, so the caller may capture it into a graph of its own; a graph of an
+ * even number of steps (with a sort: an even number of whole sort periods, begun at
+ * one) may be replayed again and again, with other such calls in between.
  * Errors: PIC_EINVAL (n_steps < 0), PIC_EDEVICE. */
 pic_status pic_step(pic_handle *h, int64_t n_steps);
 

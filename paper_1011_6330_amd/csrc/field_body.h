@@ -26,6 +26,7 @@ struct FieldArgs {
     int64_t inj_key = 0;                  // sort key of a particle injected at x = 0, u = 0
     // fused steps (k_step.hip; sc null: the counters hold the tally and the slot count)
     StepScratch *sc = nullptr;
+    int64_t *jmove = nullptr;             // receives the step's current (j itself is then jnext), see run_j
     int w_in = 0, w_add = 0, w_zero = 0;  // sc->w0 of the step that ends, of the one that begins, and to clear
     int n_in = 0;                         // sc->n of the slot count before the injection; n_in ^ 1 receives the new one
     int64_t *rec = nullptr;               // receives the slot count after the injection
@@ -138,8 +139,9 @@ __device__ __forceinline__ double gr_alpha_at(const Consts &c, double z)
 template <int GR>
 __device__ __forceinline__ double field_cell(const Consts &c, const FieldArgs &a, int64_t i)
 {
-    const int64_t N = c.N;
+    const int64_t N = c.N, jv = a.j[i];
     a.jnext[i] = 0;
+    if (a.jmove) a.jmove[i] = jv;
     double ez;
     if (c.flags & PIC_FREEZE_FIELDS) {
         ez = a.ezo[i];
@@ -162,7 +164,7 @@ __device__ __forceinline__ double field_cell(const Consts &c, const FieldArgs &a
             a.ern[0] = a.ero[0];
         }
         if (i == N - 1) a.ern[N] = a.ero[N] + c.tw * (an1 * (af * bi));
-        ez = (a.ezo[i] + c.dtR * (af * bi)) - c.c4 * (double)a.j[i];
+        ez = (a.ezo[i] + c.dtR * (af * bi)) - c.c4 * (double)jv;
     } else {
         const double bi = a.bo[i] - (c.dtdz * (a.ero[i + 1] - a.ero[i]) + c.dtR * a.ezo[i]);
         a.bn[i] = bi;
@@ -173,7 +175,7 @@ __device__ __forceinline__ double field_cell(const Consts &c, const FieldArgs &a
             a.ern[0] = a.ero[0];
         }
         if (i == N - 1) a.ern[N] = a.ero[N] + c.tw * bi;
-        ez = (a.ezo[i] + c.dtR * bi) - c.c4 * (double)a.j[i];
+        ez = (a.ezo[i] + c.dtR * bi) - c.c4 * (double)jv;
     }
     a.ezn[i] = ez;
     if (a.k32) a.k32[i] = (float)(c.qmdt * ez);
@@ -263,6 +265,7 @@ __device__ __forceinline__ double field_wave_pairs(const Consts &c, const FieldA
         *(d2 *)(a.ern + f) = d2{ern1, ern2};
         *(d2 *)(a.ezn + f) = d2{ezn1, ezn2};
         *(l2 *)(a.jnext + f) = l2{0, 0};
+        if (a.jmove) *(l2 *)(a.jmove + f) = jj[p];
         if (a.k32) *(f2 *)(a.k32 + f) = f2{(float)(c.qmdt * ezn1), (float)(c.qmdt * ezn2)};
         if (p == 0) ez_first = ezn1;
     }

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256) void k_b_from_current(Consts c, int64_t *J, do
 // B_phi = 0, J = 0, f32 kick array.
 __global__ __launch_bounds__(256) void k_fields_from_phi(Consts c, const double *phi, double *ez,
                                                          double *er, double *b, float *k32, int64_t *j0,
-                                                         int64_t *j1)
+                                                         int64_t *j1, int64_t *j2)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i > c.N) return;
@@ -142,6 +142,7 @@ __global__ __launch_bounds__(256) void k_fields_from_phi(Consts c, const double 
         if (k32) k32[i] = (float)(c.qmdt * e);
         j0[i] = 0;
         j1[i] = 0;
+        j2[i] = 0;
     }
 }
 
@@ -217,7 +218,7 @@ hipError_t launch_fields_from_phi(pic_handle *h)
     const int f = h->fbuf;
     hipLaunchKernelGGL(k_fields_from_phi, dim3(grid_for(c.N + 1, 256)), dim3(256), 0, h->stream, c,
                        w.phi, w.ez[f], w.er[f], w.b[f], h->p.precision == PIC_FP32_BULK ? w.k32 : nullptr,
-                       w.j[0], w.j[1]);
+                       w.j[0], w.j[1], w.j[2]);
     if (c.flags & PIC_B_STEADY_INIT) {
         // steady start: B_phi from the current the loaded beam carries (J is clear here)
         unsigned long long *J = (unsigned long long *)w.j[h->jbuf];

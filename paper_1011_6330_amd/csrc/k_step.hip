@@ -9,8 +9,8 @@
 // the field update, so the same bits), while the field blocks write the updated
 // fields into the other buffers; the last kernel is the field update of the last
 // step.  Nothing a kernel reads is written by it:
-//   * three current buffers take turns: step s reads J of s-1, adds to J of s, and
-//     its field blocks clear the third, J of s+1 (likewise the node-0 tallies);
+//   * three current buffers take turns (run_j): step s reads J of s-1, adds to J of s,
+//     and its field blocks clear the third, J of s+1 (likewise the node-0 tallies);
 //   * the slot count the pushes take has two words in turn (StepScratch);
 //   * the particles injected at the end of step s-1 all start from x = 0, u = 0, so
 //     the block that injects them also pushes them (push_injected), and the push
@@ -95,19 +95,19 @@ static void place_in_run(FieldArgs &f, int64_t s, bool last)
 
 static unsigned field_blocks_of(const Consts &c, int bs) { return (unsigned)((c.N + bs * FIELD_CPT - 1) / (bs * FIELD_CPT)); }
 
-hipError_t launch_run_step(pic_handle *h, int64_t s, const RunPtrs &r, bool hist, int64_t *rec)
+hipError_t launch_run_step(pic_handle *h, int64_t m, int64_t s, const RunPtrs &r, bool hist, int64_t *rec)
 {
     const Consts &c = h->c;
     Workspace &w = h->ws;
     const bool f32 = h->p.precision == PIC_FP32_BULK;
     const int jb = h->jbuf, b = h->pbuf;
-    unsigned long long *J = (unsigned long long *)w.j[run_j(jb, s)];
+    unsigned long long *J = (unsigned long long *)w.j[run_j(jb, m, s)];
     unsigned long long *cnt = hist ? (unsigned long long *)w.cell_count : nullptr;
     FieldArgs f{};
     f.ezo = r.ez; f.ero = r.er; f.bo = r.b;
     f.ezn = r.ezn; f.ern = r.ern; f.bn = r.bn;
-    f.j = s > 1 ? w.j[run_j(jb, s - 1)] : nullptr;
-    f.jnext = w.j[run_j(jb, s + 1)];
+    f.j = s > 1 ? w.j[run_j(jb, m, s - 1)] : nullptr;
+    f.jnext = w.j[run_j(jb, m, s + 1)];
     f.k32 = f32 ? w.k32 : nullptr;
     f.X = r.X; f.U = r.U; f.Xo = r.Xo; f.Uo = r.Uo;
     if (f32) { f.CL = w.cl[b]; f.OL = w.ol[b]; f.UL = w.ul[b]; }
@@ -141,8 +141,7 @@ __global__ __launch_bounds__(256) void k_run_end(Consts c, FieldArgs f)
     field_tile(c, f, blockIdx.x, 256);
 }
 
-// The closing field update of a run of m steps; the tube's current buffers then
-// stand as after single steps.
+// The closing field update of a run of m steps.
 hipError_t launch_run_end(pic_handle *h, int64_t m, const RunPtrs &r, bool hist, int64_t *rec)
 {
     const Consts &c = h->c;
@@ -152,8 +151,9 @@ hipError_t launch_run_end(pic_handle *h, int64_t m, const RunPtrs &r, bool hist,
     FieldArgs f{};
     f.ezo = r.ez; f.ero = r.er; f.bo = r.b;
     f.ezn = r.ezn; f.ern = r.ern; f.bn = r.bn;
-    f.j = w.j[run_j(jb, m)];
-    f.jnext = w.j[run_next(jb, m)];
+    f.j = w.j[run_j(jb, m, m)];
+    f.jnext = w.j[run_j(jb, m, run_moves(m) ? m : m - 1)];
+    f.jmove = run_moves(m) ? w.j[run_j(jb, m, m - 1)] : nullptr;
     f.k32 = f32 ? w.k32 : nullptr;
     f.X = r.X; f.U = r.U;
     if (f32) { f.CL = w.cl[b]; f.OL = w.ol[b]; f.UL = w.ul[b]; }
@@ -165,8 +165,7 @@ hipError_t launch_run_end(pic_handle *h, int64_t m, const RunPtrs &r, bool hist,
     f.rec = rec;
     place_in_run(f, m + 1, true);
     hipLaunchKernelGGL(k_run_end, dim3(field_blocks_of(c, 256)), dim3(256), 0, h->stream, c, f);
-    h->jlast = run_j(jb, m);
-    h->jbuf = run_next(jb, m);
+    h->jbuf ^= (int)(m & 1);
     return hipGetLastError();
 }
 
@@ -179,7 +178,7 @@ struct BatchRunArgs {
     const int64_t *pref;     // [n_tubes + 1] first block of each tube (its field blocks, then its push blocks at capacity)
     const int32_t *map;      // block -> tube
     int fb, pb;              // field and particle buffer parities
-    int j_in, j_add, j_clear;
+    int j_in, j_add, j_clear, j_move;   // j_move: -1, or the buffer that receives j_in
     int w_in, w_add, w_zero, n_in;
     int hist;                // the last step before a sort
 };
@@ -207,6 +206,7 @@ __global__ __launch_bounds__(STEP_BLOCK) void k_batch_step(BatchRunArgs r)
         f.ezn = generic(T.ez[g]); f.ern = generic(T.er[g]); f.bn = generic(T.b[g]);
         f.j = generic(T.j[r.j_in]);
         f.jnext = generic(T.j[r.j_clear]);
+        if (PART == 2 && r.j_move >= 0) f.jmove = generic(T.j[r.j_move]);
         f.ctr = ctr;
         f.sc = sc;
         f.w_in = r.w_in; f.w_add = r.w_add; f.w_zero = r.w_zero; f.n_in = r.n_in;
@@ -273,8 +273,10 @@ hipError_t launch_batch_run(pic_handle *h, int64_t m, bool hist_last)
     for (int64_t s = 1; s <= m + 1; ++s) {
         FieldArgs f{};
         place_in_run(f, s, s > m);
+        const bool move = s > m && run_moves(m);
         BatchRunArgs r{h->d_tubes, h->d_run_pref, h->d_run_map, fb, t0->pbuf,
-                       s > 1 ? run_j(jb, s - 1) : 0, s <= m ? run_j(jb, s) : 0, s <= m ? run_j(jb, s + 1) : run_next(jb, m),
+                       run_j(jb, m, s - 1), run_j(jb, m, s), run_j(jb, m, s <= m ? s + 1 : (move ? m : m - 1)),
+                       move ? run_j(jb, m, m - 1) : -1,
                        f.w_in, f.w_add, f.w_zero, f.n_in, hist_last && s >= m ? 1 : 0};
         if (f32) {
             if (s == 1) hipLaunchKernelGGL((k_batch_step<1, 0>), g, bl, 0, h->stream, r);
@@ -300,7 +302,7 @@ hipError_t launch_run(pic_handle *h, int64_t m, bool hist_last, int64_t *rec)
         const int f = h->fbuf, b = h->pbuf;
         const RunPtrs r{w.ez[f], w.er[f], w.b[f], w.ez[f ^ 1], w.er[f ^ 1], w.b[f ^ 1], w.x[b], w.u[b], w.x[b], w.u[b]};
         int64_t *n = rec ? rec + s - 1 : nullptr;
-        if (s <= m) e = launch_run_step(h, s, r, hist_last && s == m, n);
+        if (s <= m) e = launch_run_step(h, m, s, r, hist_last && s == m, n);
         else e = launch_run_end(h, m, r, hist_last, n);
         if (s > 1) h->fbuf ^= 1;
     }

@@ -202,7 +202,7 @@ struct Workspace {
     long long *stage_base;      // [2] slot counts of the two streams before the append
     long long *total_lo;    // FP32-bulk sort: low-destination total
     double *ez[2], *er[2], *b[2];
-    int64_t *j[3];          // fixed-point current: the next step's (clear), the last step's, and a third for fused steps
+    int64_t *j[3];          // fixed-point current, ping-pong per step; the third serves fused steps and is clear between calls
     double *rho_gj;
     int64_t *w;             // CIC node weights (Poisson, diagnostics)
     double *phi, *cp, *dp, *rhs;
@@ -321,13 +321,8 @@ struct AdjRecord {
     double loss = 0.0, forward_ms = 0.0;
     int64_t step_end = 0;       // the tube's step count after the forward
     int64_t mut = 0;            // the tube's change count after the forward
-    int jb_final = 0, jl_final = 1;   // current buffers (next, last) after the forward
+    int jb_final = 0;           // current buffer parity after the forward
     int64_t held[2] = {-1, -1}; // segment whose states each set of the tape's slots holds (-1: none)
-};
-
-// Buffers after a captured round.
-struct GraphEnd {
-    int fbuf, jbuf, jlast, pbuf;
 };
 
 struct pic_handle {
@@ -339,8 +334,7 @@ struct pic_handle {
     hipStream_t stream = nullptr;
     int pbuf = 0;       // current particle buffer
     int fbuf = 0;       // field buffer holding E^n, B^{n-1/2}
-    int jbuf = 0;       // current buffer that the next step deposits into (0 or 1, clear)
-    int jlast = 1;      // current buffer of the last step
+    int jbuf = 0;       // current buffer that the next step deposits into (clear); 1 - jbuf holds the last step's
     bool bins_clear = false;     // every profile bin of the workspace is clear
     bool counts_clear = false;   // the sort key counts (a batch: every tube's) are zero
     int64_t step = 0;   // steps enqueued
@@ -378,7 +372,6 @@ struct pic_handle {
     int batch_block = 256, batch_ppt = 2;
     int64_t batch_push_items = 0, batch_field_items = 0, batch_sort_items = 0, batch_keys = 0, batch_scan_blocks = 0;
     hipGraphExec_t graph[8] = {};   // one round, keyed by the (field, current, particle) buffer parities
-    GraphEnd graph_end[8] = {};
     bool use_graph = true;
 };
 
@@ -410,21 +403,30 @@ struct RunPtrs {
     double *ezn, *ern, *bn;
     double *X, *U, *Xo, *Uo;
 };
-// Kernel s of a run (s = 1: the push of the first step; s > 1: the field update of
-// step s - 1 and the push of step s), the closing field update of a run of m steps
+// Kernel s of a run of m steps (s = 1: the push of the first step; s > 1: the field update of
+// step s - 1 and the push of step s), its closing field update
 // (which moves the tube's current buffers on), and a whole run in place.
-hipError_t launch_run_step(pic_handle *h, int64_t s, const RunPtrs &r, bool hist, int64_t *rec);
+hipError_t launch_run_step(pic_handle *h, int64_t m, int64_t s, const RunPtrs &r, bool hist, int64_t *rec);
 hipError_t launch_run_end(pic_handle *h, int64_t m, const RunPtrs &r, bool hist, int64_t *rec);
 hipError_t launch_run(pic_handle *h, int64_t m, bool hist_last, int64_t *rec = nullptr);
 // The same for a batch; blocks of one of its tubes in a run's kernels.
 hipError_t launch_batch_run(pic_handle *h, int64_t m, bool hist_last);
 int64_t run_blocks(const pic_params &p);
 int64_t run_slots(const pic_params &p);
-// Current buffers of a run that starts with jb clear: step s (from 1) adds to
-// run_j(jb, s); after m steps run_j(jb, m) holds the last current and run_next(jb, m)
-// is clear.
-inline int run_j(int jb, int64_t s) { return (s - 1) % 3 == 0 ? jb : ((s - 1) % 3 == 1 ? 2 : 1 - jb); }
-inline int run_next(int jb, int64_t m) { return run_j(jb, m) == jb ? 1 - jb : jb; }
+// Current buffers of a run of m steps: step s (0: the one before the first, m + 1: the
+// one after the last) adds to run_j(jb, m, s).  Before and after a run they stand as
+// single steps leave them, since steps captured into a caller's graph hold the buffers
+// of that parity: jb clear, the last current in 1 - jb, buffer 2 clear; m steps turn jb
+// into jb ^ (m & 1).  The three take turns in one of six orders that begins with a clear
+// buffer and ends with the last current in its place; for m = 4, 10, 16, ... none does,
+// and the closing field update moves it there from buffer 2 (run_moves).
+inline int run_j(int jb, int64_t m, int64_t s)
+{
+    constexpr int order[6][3] = {{0, 2, 1}, {0, 1, 2}, {0, 1, 2}, {2, 1, 0}, {2, 0, 1}, {2, 0, 1}};   // 0: jb, 1: 1 - jb
+    const int k = order[m % 6][(s + 2) % 3];
+    return k == 2 ? 2 : k ^ jb;
+}
+inline bool run_moves(int64_t m) { return m % 6 == 4; }
 // Profile bins: count, 128-bit sum (low and high words), ordered bit images of min and max.
 struct ProfPtrs {
     long long *cnt;

@@ -632,14 +632,29 @@ static void free_batch_graphs(pic_handle *h);
 // Small tubes take their steps in fused runs (k_step.hip).
 static bool fused(const pic_handle *h) { return run_slots(h->p) <= FUSE_SLOTS && !(h->c.flags & PIC_GR_ALPHA); }
 
+// The caller is capturing the stream into a graph: what is enqueued runs at that
+// graph's replays, and not now.
+static bool captured(const pic_handle *h)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!h->stream || hipStreamIsCapturing(h->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // m steps of a single tube, launched directly, of which only the last may be
 // followed by a sort (its push counts the sort keys): fused, or step by step push
-// and field update + injection.
-static pic_status tube_steps_direct(pic_handle *h, int64_t m)
+// and field update + injection.  In a caller's capture the graph clears the key counts
+// itself, and whether they are clear now stays as it is.
+static pic_status tube_steps_direct(pic_handle *h, int64_t m, bool in_capture = false)
 {
     const bool sort_after = h->p.sort_every > 0 && (h->step + m) % h->p.sort_every == 0;
-    if (sort_after) HIP_OK(launch_clear_hist(h));
-    if (sort_after) h->counts_clear = false;   // until the sort has cleared them
+    const bool clear = h->counts_clear;
+    if (sort_after) {
+        if (in_capture) h->counts_clear = false;
+        HIP_OK(launch_clear_hist(h));
+        h->counts_clear = false;   // until the sort has cleared them
+    }
     if (m > 1 && fused(h)) {
         HIP_OK(launch_run(h, m, sort_after));
     } else {
@@ -650,12 +665,14 @@ static pic_status tube_steps_direct(pic_handle *h, int64_t m)
             h->hist_on = false;
             HIP_OK(e2);
             h->fbuf ^= 1;
-            h->jlast = h->jbuf;
             h->jbuf ^= 1;
         }
     }
     h->step += m;
-    if (sort_after) HIP_OK(launch_sort(h));
+    if (sort_after) {
+        HIP_OK(launch_sort(h));
+        if (in_capture) h->counts_clear = clear;
+    }
     return PIC_OK;
 }
 
@@ -682,18 +699,18 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
     // in the parity state it started from).
     const bool sorts = h->p.sort_every > 0;
     const int64_t S = sorts ? h->p.sort_every : GRAPH_ROUND;
+    const bool in_capture = captured(h);
     while (n_steps > 0) {
-        if (S > 1 && h->use_graph && h->step % S == 0 && n_steps >= S) {
+        if (S > 1 && h->use_graph && !in_capture && h->step % S == 0 && n_steps >= S) {
             const int key = h->fbuf | (h->jbuf << 1) | (h->pbuf << 2);
             if (sorts) HIP_OK(launch_clear_hist(h));   // no part of the captured round
             if (!h->graph[key]) {
-                const int fb = h->fbuf, jb = h->jbuf, jl = h->jlast, pb = h->pbuf;
+                const int fb = h->fbuf, jb = h->jbuf, pb = h->pbuf;
                 const int64_t st = h->step;
                 hipGraph_t g = nullptr;
                 bool ok = hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
                 if (ok) {
                     const pic_status rc = tube_steps_direct(h, S);
-                    h->graph_end[key] = GraphEnd{h->fbuf, h->jbuf, h->jlast, h->pbuf};
                     const hipError_t e = hipStreamEndCapture(h->stream, &g);
                     ok = rc == PIC_OK && e == hipSuccess && g &&
                          hipGraphInstantiate(&h->graph[key], g, nullptr, nullptr, 0) == hipSuccess;
@@ -702,7 +719,6 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
                 // the captured round has not run yet
                 h->fbuf = fb;
                 h->jbuf = jb;
-                h->jlast = jl;
                 h->pbuf = pb;
                 h->step = st;
                 if (!ok) {
@@ -713,16 +729,14 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
                 }
             }
             HIP_OK(hipGraphLaunch(h->graph[key], h->stream));
-            const GraphEnd &g = h->graph_end[key];
-            h->fbuf = g.fbuf;
-            h->jbuf = g.jbuf;
-            h->jlast = g.jlast;
-            h->pbuf = g.pbuf;
+            h->fbuf ^= (int)(S & 1);
+            h->jbuf ^= (int)(S & 1);
+            if (sorts) h->pbuf ^= 1;
             h->step += S;
             n_steps -= S;
         } else {
             const int64_t left = S - h->step % S, m = n_steps < left ? n_steps : left;
-            if (pic_status rc = tube_steps_direct(h, m)) return rc;
+            if (pic_status rc = tube_steps_direct(h, m, in_capture)) return rc;
             n_steps -= m;
         }
     }
@@ -797,7 +811,6 @@ pic_status pic_step_timed(pic_handle *h, int64_t n_steps, pic_timing *out)
             break;
         }
         h->fbuf ^= 1;
-        h->jlast = h->jbuf;
         h->jbuf ^= 1;
         h->step += 1;
         const bool sorted = sort_after;
@@ -947,7 +960,7 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
                           {out->er, w.er[f], (size_t)(N + 1) * 8},
                           {out->b_phi, w.b[f], (size_t)N * 8},
                           {out->rho_gj, w.rho_gj, (size_t)(N + 1) * 8},
-                          {out->j_last, w.j[h->jlast], (size_t)N * 8},
+                          {out->j_last, w.j[1 - h->jbuf], (size_t)N * 8},
                           {out->weights, w.w, (size_t)(N + 1) * 8},
                           {gdst, w.gauss, (size_t)(N + 1) * 8}};
     Want packed[13];
@@ -1278,7 +1291,7 @@ pic_status pic_save(pic_handle *h, void *buf, size_t cap, size_t *bytes)
     HIP_OK(d2h(L.ez, w.ez[f], (size_t)N * 8));
     HIP_OK(d2h(L.er, w.er[f], (size_t)(N + 1) * 8));
     HIP_OK(d2h(L.b, w.b[f], (size_t)N * 8));
-    HIP_OK(d2h(L.j, w.j[h->jlast], (size_t)N * 8));
+    HIP_OK(d2h(L.j, w.j[1 - h->jbuf], (size_t)N * 8));
     if (!f32) {
         HIP_OK(d2h(L.p[0], w.x[b], (size_t)nlo * 8));
         HIP_OK(d2h(L.p[1], w.u[b], (size_t)nlo * 8));
@@ -1344,7 +1357,7 @@ pic_status pic_load(pic_handle *h, const void *buf, size_t bytes)
     HIP_OK(h2d(w.ez[f], L.ez, (size_t)N * 8));
     HIP_OK(h2d(w.er[f], L.er, (size_t)(N + 1) * 8));
     HIP_OK(h2d(w.b[f], L.b, (size_t)N * 8));
-    HIP_OK(h2d(w.j[h->jlast], L.j, (size_t)N * 8));
+    HIP_OK(h2d(w.j[1 - h->jbuf], L.j, (size_t)N * 8));
     HIP_OK(launch_zero_i64(h, w.j[h->jbuf], N));        // the next step deposits into a cleared J
     if (!f32) {
         HIP_OK(h2d(w.x[b], L.p[0], (size_t)hd.n_lo * 8));
@@ -1648,6 +1661,7 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
     if (pic_status sp = batch_resolve_pending(h)) return sp;
     pic_handle *t0 = h->tubes[0];
     const int64_t S = t0->p.sort_every;
+    const bool in_capture = captured(h);
     while (n > 0) {
         int64_t r;
         if (S > 0) {
@@ -1659,7 +1673,9 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
         const bool to_sort = S > 0 && (t0->step + r) % S == 0;
         const bool run = h->batch_run_blocks > 0 && r > 1 && !ev;   // fused steps (timed runs measure push and field apart)
         const int key = t0->fbuf | (t0->jbuf << 1) | (t0->pbuf << 2);
-        const bool round = to_sort && r == S && h->use_graph && !ev;
+        const bool round = to_sort && r == S && h->use_graph && !ev && !in_capture;
+        const bool clear = h->counts_clear;
+        if (to_sort && in_capture) h->counts_clear = false;   // as in tube_steps_direct
         if (to_sort) HIP_OK(launch_batch_clear(h));
         if (round && !h->graph[key]) {
             hipGraph_t g = nullptr;
@@ -1698,6 +1714,7 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
             }
             if (e) HIP_OK(hipEventRecord(e[ne - 2], h->stream));
             if (to_sort) HIP_OK(launch_batch_sort(h));
+            if (to_sort && in_capture) h->counts_clear = clear;
             if (e) HIP_OK(hipEventRecord(e[ne - 1], h->stream));
             if (tim) {
                 tim->push_launches += r;
@@ -1708,8 +1725,7 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
         }
         for (pic_handle *t : h->tubes) {
             t->fbuf ^= (int)(r & 1);
-            t->jlast = run ? run_j(t->jbuf, r) : (t->jbuf ^ (int)((r - 1) & 1));
-            t->jbuf = run ? run_next(t->jbuf, r) : (t->jbuf ^ (int)(r & 1));
+            t->jbuf ^= (int)(r & 1);
             t->step += r;
             if (to_sort) t->pbuf ^= 1;
         }
@@ -1865,7 +1881,7 @@ hipError_t launch_run_recorded(pic_handle *h, const SegSlots &g, int64_t m, int6
             p.Xo = s == m ? w.x[b] : g.x(s);
             p.Uo = s == m ? w.u[b] : g.u(s);
         }
-        e = end ? launch_run_end(h, m, p, false, rec + s - 1) : launch_run_step(h, s, p, false, rec + s - 1);
+        e = end ? launch_run_end(h, m, p, false, rec + s - 1) : launch_run_step(h, m, s, p, false, rec + s - 1);
     }
     h->fbuf = f;
     return e;
@@ -1921,7 +1937,7 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
     // keep what the recompute overwrites: counters and the last step's current
     CopySegs keep{};
     keep.add(t.final_ctr, w.ctr, CTR_WORDS);
-    keep.add(t.final_jlast, w.j[h->jlast], N);
+    keep.add(t.final_jlast, w.j[1 - h->jbuf], N);
     FWD_OK(launch_copy_segs(h, keep));
     FWD_OK(hipEventRecord(ev[1], h->stream));
     DevCounters c1;
@@ -1948,7 +1964,6 @@ pic_status adjoint_forward(pic_handle *h, int64_t T, int64_t K, void *d_tape, si
     r.step_end = h->step;
     r.mut = h->mut;
     r.jb_final = h->jbuf;
-    r.jl_final = h->jlast;
     r.forward_ms = fms;
     return done(PIC_OK);
 }
@@ -2029,14 +2044,13 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
         // a fused run of the segment's steps but the last: kernel s pushes from slot
         // s-1 to slot s and makes the field update from slot s-2 to slot s-1
         h->jbuf = 0;
-        h->jlast = 1;
         for (int64_t s = 1; m > 1 && s <= m && e == hipSuccess; ++s) {
             const int64_t o = s > 1 ? s - 2 : 0, n = s > 1 ? s - 1 : 0;
             RunPtrs p{g.ez(o), g.er(o), g.b(o), g.ez(n), g.er(n), g.b(n), g.x(s - 1), g.u(s - 1), nullptr, nullptr};
             if (s < m) {
                 p.Xo = g.x(s);
                 p.Uo = g.u(s);
-                e = launch_run_step(h, s, p, false, nullptr);
+                e = launch_run_step(h, m - 1, s, p, false, nullptr);
             } else {
                 e = launch_run_end(h, m - 1, p, false, nullptr);
             }
@@ -2084,11 +2098,10 @@ pic_status adjoint_backward(pic_handle *h, double dloss, pic_adjoint_out *out)
     ADJ_OK(hipEventRecord(ev[1], h->stream));
     // restore the end state the forward left
     h->jbuf = r.jb_final;
-    h->jlast = r.jl_final;
     CopySegs end{};
     end.add(w.ctr, t.final_ctr, CTR_WORDS);
     end.add(w.j[h->jbuf], nullptr, N);
-    end.add(w.j[h->jlast], t.final_jlast, N);
+    end.add(w.j[1 - h->jbuf], t.final_jlast, N);
     ADJ_OK(launch_copy_segs(h, end));
     // results
     std::vector<double> params((size_t)h->c.n_knots + 2);
