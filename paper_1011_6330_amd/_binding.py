@@ -9,6 +9,7 @@ A tube is described by a dict with the keys of ``pic_params`` (see
 """
 import ctypes
 import os
+import threading
 
 import numpy as np
 
@@ -211,32 +212,80 @@ class _TubeOps:
         return buf.raw[:n.value]
 
 
-# Streams of closed tubes and batches, per device, for the next ones: a stream's first
-# work costs 0.15 ms and its first copy of megabytes from pageable memory 1.3 ms more (a
-# warm start of 1e6 particles on a new stream took 3.05 ms, on a used one 1.59).  A
-# stream is idle when it comes here (pic_destroy waits for it), and torch itself has no
-# more than 32 to give.
-_idle_streams = {}
+class _StreamPool:
+    """Streams of closed tubes and batches, per device, for the next ones: a stream's first
+    work costs 0.15 ms and its first copy of megabytes from pageable memory 1.3 ms more (a
+    warm start of 1e6 particles on a new stream took 3.05 ms, on a used one 1.59).
+
+    torch hands out the same 32 streams of a device in turn, so a stream is known here by
+    its handle (``cuda_stream``), with the number of open tubes and batches that work on
+    it.  Idle are those that were made here and that no open one uses, each once; a stream
+    that a caller has given is the caller's and is not handed out.  While fewer than 32
+    are in use, every tube and batch gets one that no other uses.  (Two that share one are
+    in order with each other; driven by two threads, what one enqueues while the other
+    captures a round would become part of that round.)"""
+
+    def __init__(self):
+        self._lock = threading.RLock()   # a tube collected while it is held closes in the same thread
+        self._idle = {}                  # (device, handle) -> stream, the last given back taken first
+        self._open = {}                  # (device, handle) -> [open users, stream or None if it is a caller's]
+
+    def take(self, device, make):
+        """An idle stream of the device, else one from ``make`` that no open user has."""
+        with self._lock:
+            for key in reversed(self._idle):
+                if key[0] == device:
+                    stream = self._idle.pop(key)
+                    break
+            else:
+                stream = make()
+                for _ in range(31):
+                    if (device, int(stream.cuda_stream)) not in self._open:
+                        break
+                    stream = make()
+            return self._use(device, stream, False)
+
+    def use(self, device, stream):
+        """Notes an open user of a caller's stream."""
+        with self._lock:
+            return self._use(device, stream, True)
+
+    def _use(self, device, stream, given):
+        key = (device, int(stream.cuda_stream))
+        self._idle.pop(key, None)
+        entry = self._open.setdefault(key, [0, stream])
+        entry[0] += 1
+        if given:
+            entry[1] = None
+        return key, stream
+
+    def release(self, key):
+        """An open user has closed (its work on the stream is done)."""
+        with self._lock:
+            entry = self._open[key]
+            entry[0] -= 1
+            if entry[0] == 0:
+                del self._open[key]
+                if entry[1] is not None:
+                    self._idle[key] = entry[1]
 
 
-def _take_stream(device):
+_streams = _StreamPool()
+
+
+def _open_stream(stream, device):
+    """(key in the pool, stream) for a new tube or batch on the current device."""
     import torch
-    try:
-        return _idle_streams[torch.cuda.current_device()].pop()
-    except (KeyError, IndexError):
-        return torch.cuda.Stream(device)
-
-
-def _give_stream(stream):
-    idle = _idle_streams.setdefault(stream.device_index, [])
-    if len(idle) < 32:
-        idle.append(stream)
+    dev = torch.cuda.current_device()
+    if stream is not None:
+        return _streams.use(dev, stream)
+    return _streams.take(dev, lambda: torch.cuda.Stream(device))
 
 
 class Tube(_TubeOps):
     """One tube on the GPU.  The workspace is a torch uint8 tensor on ``device``
     and all work is ordered on ``stream`` (a torch.cuda.Stream; when not given, a closed
-    tube's or a new one, of the default priority)."""
+    tube's or a new one, of the default priority, and another tube's after close())."""
 
     def __init__(self, cfg=None, device="cuda", stream=None, **kw):
         import torch
@@ -248,12 +297,15 @@ class Tube(_TubeOps):
         self.device = torch.device(device)
         nbytes = workspace_bytes(self.cfg)
         with torch.cuda.device(self.device):
-            self.stream = stream if stream is not None else _take_stream(self.device)
-            self._own_stream = stream is None
             self.ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            self._stream_key, self.stream = _open_stream(stream, self.device)
         self._h = ctypes.c_void_p()
-        _check(self.lib.pic_init(ctypes.byref(self.params), ctypes.c_void_p(self.ws.data_ptr()), nbytes,
-                                 ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(self._h)), "pic_init")
+        try:
+            _check(self.lib.pic_init(ctypes.byref(self.params), ctypes.c_void_p(self.ws.data_ptr()), nbytes,
+                                     ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(self._h)), "pic_init")
+        except BaseException:
+            _streams.release(self._stream_key)
+            raise
 
     def step(self, n=1):
         _check(self.lib.pic_step(self._h, int(n)), "pic_step")
@@ -399,9 +451,7 @@ class Tube(_TubeOps):
         if getattr(self, "_h", None) and self._h.value:
             self.lib.pic_destroy(self._h)
             self._h = ctypes.c_void_p()
-            if self._own_stream:
-                self._own_stream = False
-                _give_stream(self.stream)
+            _streams.release(self._stream_key)
 
     def __del__(self):
         try:
@@ -456,13 +506,16 @@ class Batch:
             raise PicError(-1, "pic_batch_workspace_bytes", self.lib.pic_last_error().decode())
         self.device = torch.device(device)
         with torch.cuda.device(self.device):
-            self.stream = stream if stream is not None else _take_stream(self.device)
-            self._own_stream = stream is None
             self.ws = torch.empty(n, dtype=torch.uint8, device=self.device)
+            self._stream_key, self.stream = _open_stream(stream, self.device)
         self._h = ctypes.c_void_p()
-        _check(self.lib.pic_init_batch(arr, len(made), ctypes.c_void_p(self.ws.data_ptr()), n,
-                                       ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(self._h)),
-               "pic_init_batch")
+        try:
+            _check(self.lib.pic_init_batch(arr, len(made), ctypes.c_void_p(self.ws.data_ptr()), n,
+                                           ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(self._h)),
+                   "pic_init_batch")
+        except BaseException:
+            _streams.release(self._stream_key)
+            raise
         self.tubes = [_TubeView(self, t) for t in range(len(made))]
 
     @property
@@ -498,9 +551,7 @@ class Batch:
                 t.close()
             self.lib.pic_destroy(self._h)
             self._h = ctypes.c_void_p()
-            if self._own_stream:
-                self._own_stream = False
-                _give_stream(self.stream)
+            _streams.release(self._stream_key)
 
     def __del__(self):
         try:
