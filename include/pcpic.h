@@ -297,7 +297,7 @@ enum {
  * slots apart.  FP32-bulk: 4 (4 consecutive low-stream slots per thread; in
  * the high stream two pairs of slots 128 apart).  pic_init sets 128 x 2 (FP64) or
  * 128 x 4 (FP32-bulk), with PIC_PUSH_NONTEMPORAL where the particle streams at
- * capacity take more than 1 GiB.  Tubes small enough for fused steps (k_step.hip)
+ * capacity take up to 32 MiB or more than 1 GiB.  Tubes small enough for fused steps (k_step.hip)
  * have one shape of their own there.
  * Results do not depend on the choice (integer deposition); the autotuner
  * picks the fastest.  Errors: PIC_EINVAL for an unsupported shape or flag. */

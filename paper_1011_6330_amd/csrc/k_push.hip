@@ -30,15 +30,14 @@
 
 namespace pcpic {
 
-// rev: the tiles in descending order (push_order); the idle blocks come last either way.
+// rev: the tiles in descending order (push_order, push_tile).
 template <int BLOCK, int PPT, int NT, int GR = 0>
 __global__ __launch_bounds__(BLOCK) void k_push_f64(Consts c, PushArgs a, int rev)
 {
     constexpr int64_t TILE = BLOCK * PPT;
     const int64_t n = a.ctr->n_slots;
-    const int64_t k = blockIdx.x;
-    if (k * TILE >= n) return;                    // whole block idle (uniform)
-    const int64_t tile0 = (rev ? (n - 1) / TILE - k : k) * TILE;
+    const int64_t tile0 = push_tile(blockIdx.x, (n + TILE - 1) / TILE, rev) * TILE;
+    if (tile0 < 0 || tile0 >= n) return;          // whole block idle (uniform)
     push_tile_f64<BLOCK, PPT, NT, GR>(c, a, n, tile0);
 }
 
@@ -49,7 +48,7 @@ static hipError_t launch_push_t(pic_handle *h)
                (unsigned long long *)h->ws.j[h->jbuf], h->ws.ctr, (unsigned long long *)&h->ws.ctr->w0,
                h->hist_on ? (unsigned long long *)h->ws.cell_count : nullptr};
     const int64_t tile = (int64_t)BLOCK * PPT;
-    const unsigned grid = (unsigned)((h->c.cap + tile - 1) / tile);
+    const unsigned grid = push_blocks((h->c.cap + tile - 1) / tile);
     hipLaunchKernelGGL((k_push_f64<BLOCK, PPT, NT, GR>), dim3(grid), dim3(BLOCK), 0, h->stream, h->c, a, push_order(h));
     return hipGetLastError();
 }

@@ -23,16 +23,16 @@
 
 namespace pcpic {
 
-// rev: the items in descending order (push_order); the idle blocks come last either way.
+// rev: the items in descending order (push_order, push_tile).
 template <int BLOCK, int NT>
 __global__ __launch_bounds__(BLOCK) void k_push_f32(Consts c, Push32Args a, int rev)
 {
     constexpr int64_t SPAN = (int64_t)BLOCK * F32_PPT_LO;
     static_assert(F32_PPT_LO == F32_PPT_HI, "one item size for both streams");
     const int64_t n_lo = a.ctr->n_slots, n_hi = a.ctr->n_slots_hi;
-    const int64_t items = (n_lo + SPAN - 1) / SPAN + (n_hi + SPAN - 1) / SPAN, k = blockIdx.x;
-    if (k >= items) return;
-    push_item_f32<BLOCK, NT>(c, a, rev ? items - 1 - k : k, n_lo, n_hi);
+    const int64_t items = (n_lo + SPAN - 1) / SPAN + (n_hi + SPAN - 1) / SPAN, k = push_tile(blockIdx.x, items, rev);
+    if (k < 0 || k >= items) return;
+    push_item_f32<BLOCK, NT>(c, a, k, n_lo, n_hi);
 }
 
 // ------------------------------------------------------------------------
@@ -186,7 +186,7 @@ static hipError_t launch_push32_t(pic_handle *h)
     const Workspace &w = h->ws;
     const int b = h->pbuf;
     const int64_t tile_hi = (int64_t)BLOCK * F32_PPT_HI;
-    const unsigned items = (unsigned)((h->c.cap + tile_hi - 1) / tile_hi + 1);   // both streams, any split
+    const unsigned items = push_blocks((h->c.cap + tile_hi - 1) / tile_hi + 1);   // both streams, any split
     Push32Args a{w.cl[b], w.ol[b], w.ul[b], w.hp[b], w.hw[b], w.hg[b], w.uh[b], w.k32, w.ez[h->fbuf],
                  (unsigned long long *)w.j[h->jbuf], w.ctr, (unsigned long long *)&w.ctr->w0,
                  h->hist_on ? (unsigned long long *)w.cell_count : nullptr, h->u_hi};

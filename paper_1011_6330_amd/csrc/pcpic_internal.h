@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "pcpic.h"
+#include "step_route.h"
 
 namespace pcpic {
 
@@ -340,7 +341,7 @@ struct pic_handle {
     int64_t step = 0;   // steps enqueued
     int push_block = 64;
     int push_ppt = 2;
-    int push_nt = 1;    // nontemporal particle-stream access (pic_init: past CACHED_BYTES)
+    int push_nt = 1;    // nontemporal particle-stream access (pic_init: push_nontemporal)
     double u_hi = 0.0;  // FP32-bulk: |u| from which a particle belongs to the FP64 stream
     int push_grid = 0;  // 0 = derived from the device
     const int64_t *d_sched = nullptr;   // replayed injection counts (caller's device array)
@@ -383,17 +384,9 @@ hipError_t launch_poisson(pic_handle *h);
 hipError_t launch_poisson_rhs(pic_handle *h);
 hipError_t launch_fields_from_phi(pic_handle *h);
 hipError_t launch_thomas_batch(pic_handle *b, const int32_t *d_list, int n);
-// Order of a single tube's push over its slots: ascending and descending in turn (the
-// field buffer's parity alternates with the steps).  What one step touched last the
-// next touches first, while it is still in the 256 MiB last-level cache; for that the
-// streams are read and written with plain accesses where they take up to CACHED_BYTES
-// (nontemporal ones pass the cache by).  Per step, ascending and nontemporal against
-// both: 4.6e6 particles in FP64 (73 MB) 35.6 -> 33.7 us, 4e7 (0.64 GB) 224 -> 212, 5.9e7
-// (0.94 GB) 332 -> 330; past that the plain accesses cost more than the cache gives
-// (8.5e7, 1.36 GB: 478 -> 483).  FP32-bulk, 4e7 (0.48 GB) 179 -> 170, 5.9e7 259 -> 253,
-// 1.3e8 (1.57 GB) 539 -> 557.
+// Order of a single tube's push over its slots (step_route.h): ascending and descending
+// in turn, as the field buffer's parity alternates with the steps.
 inline int push_order(const pic_handle *h) { return h->fbuf; }
-constexpr int64_t CACHED_BYTES = (int64_t)1 << 30;
 hipError_t launch_push_f64(pic_handle *h);
 hipError_t launch_push_f32(pic_handle *h);
 // Fused steps (k_step.hip).  Fields before (ez, er, b) and after (ezn, ern, bn) the

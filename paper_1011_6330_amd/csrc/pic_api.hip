@@ -426,7 +426,7 @@ static pic_status init_tube(const pic_params *p, void *d_workspace, size_t ws_by
     // the fastest measured push shapes
     h->push_block = 128;
     h->push_ppt = p->precision == PIC_FP32_BULK ? 4 : 2;
-    h->push_nt = p->capacity > CACHED_BYTES / (p->precision == PIC_FP32_BULK ? 12 : 16) ? 1 : 0;   // push_order
+    h->push_nt = push_nontemporal(p->capacity * (p->precision == PIC_FP32_BULK ? 12 : 16)) ? 1 : 0;
     {
         const double g = p->gamma_fp64 > 0.0 ? p->gamma_fp64 : 1e6;
         h->u_hi = sqrt(g * g - 1.0);   // gamma >= g  <=>  |u| >= sqrt(g^2 - 1)

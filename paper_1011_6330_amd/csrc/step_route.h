@@ -1,0 +1,35 @@
+// step_route.h -- rules of the step's launches: plain C++, so that they can be tested
+// without a GPU (constexpr functions are device functions too).
+#pragma once
+
+#include <stdint.h>
+
+namespace pcpic {
+
+// Order of a single tube's push over its slots: ascending and descending in turn.  What
+// one step touched last the next touches first, while it is still in the 256 MiB
+// last-level cache.  Blocks go to the 8 XCDs in turn, each with an L2 of 4 MiB: the
+// descending order reverses groups of 8 tiles and keeps a tile on the XCD that had it
+// the step before.  (Reversed tile by tile, every tile changed its XCD: 1e6 FP64
+// particles took 16.3 us a step where ascending ones take 13.0, and 9e6 took 53.1 where
+// this order takes 50.4.)
+// The streams are read and written with plain accesses where they take more than the
+// L2s and up to CACHED_BYTES (nontemporal ones pass the last-level cache by).  Per step
+// in this order, nontemporal / plain, and ascending and nontemporal: FP64 particles
+// 1e6 (16 MB) 12.8 / 13.5, 12.9; 2e6 19.7 / 18.4, 19.7; 4.6e6 33.2 / 30.5, 34.4; 9e6
+// 56.9 / 50.4, 58.6; 4e7 (0.64 GB) 223.5 / 212.1, 231.1; FP32-bulk 1.4e6 (17 MB) 14.4 /
+// 15.1, 14.5; 2.8e6 20.6 / 20.1, 21.3; 4e7 172.1 / 159.4, 177.6.  Past 1 GiB they are
+// within 1% (FP64 8.5e7, 1.36 GB: 473 / 468; FP32-bulk 1.3e8, 1.56 GB: 531 / 535).
+constexpr int64_t CACHED_BYTES = (int64_t)1 << 30, L2_BYTES = (int64_t)32 << 20;
+constexpr bool push_nontemporal(int64_t bytes) { return bytes <= L2_BYTES || bytes > CACHED_BYTES; }
+
+constexpr int XCDS = 8;
+// The tile of block k of `tiles` (past the ends, < 0 or >= tiles: the block is idle), and
+// the blocks to launch for them.
+constexpr int64_t push_tile(int64_t k, int64_t tiles, int rev)
+{
+    return rev ? ((tiles + XCDS - 1) / XCDS - 1 - k / XCDS) * XCDS + k % XCDS : k;
+}
+constexpr unsigned push_blocks(int64_t tiles) { return (unsigned)((tiles + XCDS - 1) / XCDS * XCDS); }
+
+}  // namespace pcpic

@@ -1,0 +1,53 @@
+"""The rules of csrc/step_route.h, compiled for the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _run(tmp_path, body):
+    src, exe = tmp_path / "route.cpp", tmp_path / "route"
+    src.write_text('#include "step_route.h"\n#include <stdio.h>\n#include <vector>\nusing namespace pcpic;\n'
+                   "#define CHECK(x) do { if (!(x)) { printf(\"line %d: %s\\n\", __LINE__, #x); return 1; } } while (0)\n"
+                   "int main()\n{\n" + body + "\n    return 0;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_1011_6330_amd", "csrc"), str(src), "-o",
+                    str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout
+
+
+needs_gxx = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@needs_gxx
+def test_push_order_takes_each_tile_once_on_its_xcd(tmp_path):
+    """Both orders cover every tile exactly once within the launched blocks, whatever the
+    capacity's grid; a tile stays on the XCD (block index mod 8) of the ascending order; and
+    the descending one starts within 8 tiles of the last."""
+    _run(tmp_path, """
+    for (int64_t tiles = 0; tiles < 70; ++tiles)
+        for (int64_t cap = tiles; cap < tiles + 20; ++cap)
+            for (int rev = 0; rev < 2; ++rev) {
+                std::vector<int> seen((size_t)tiles, 0);
+                for (int64_t k = 0; k < (int64_t)push_blocks(cap); ++k) {
+                    const int64_t t = push_tile(k, tiles, rev);
+                    if (t < 0 || t >= tiles) continue;
+                    ++seen[(size_t)t];
+                    CHECK(t % XCDS == k % XCDS);
+                    if (rev && k < XCDS) CHECK(t >= tiles - XCDS);
+                }
+                for (int s : seen) CHECK(s == 1);
+            }
+""")
+
+
+@needs_gxx
+def test_push_access_rule(tmp_path):
+    _run(tmp_path, """
+    CHECK(push_nontemporal(0) && push_nontemporal((int64_t)32 << 20) && !push_nontemporal(((int64_t)32 << 20) + 1));
+    CHECK(!push_nontemporal((int64_t)1 << 30) && push_nontemporal(((int64_t)1 << 30) + 1));
+    CHECK(push_nontemporal(((int64_t)1 << 62)));
+""")
