@@ -1,7 +1,7 @@
 // k_batch.hip -- many independent tubes of uneven size stepped together.
 //
 // Each tube keeps the exact workspace layout of a single tube; a device table
-// of TubeDev descriptors points at them.  A batch of up to FUSE_SLOTS expected slots
+// of TubeDev descriptors points at them.  A batch of up to fuse_slots expected slots
 // takes its steps in fused runs, one kernel per step (k_step.hip).  In a larger one a
 // step is a work list and two kernels over it, one block per item:
 //   push  -- items = particle tiles of every tube (both streams in FP32-bulk

@@ -19,11 +19,9 @@
 // (4e3 particles) take 4.4 and 3.0 us, a chain of dependent memory latencies each,
 // where an empty kernel of a graph takes 1.7.  Per step with its share of the sort
 // (every 64 steps), push and field kernels against fused: 2e5 particles 10.7 -> 6.6
-// us, 6e5 11.4 -> 8.6, 1.2e6 15.1 -> 12.6, 3.6e6 29.7 -> 29.2 (FP32-bulk 26.8 ->
-// 25.8), 6.6e6 43.2 -> 46.3 (37.7 -> 39.0): FUSE_SLOTS lies between the last two, where
-// forming the kicks per wave starts to cost more than a kernel.  It is compared with
-// the slots that a tube is expected to fill (run_slots), not with its capacity: eight
-// cold tubes of 11,036 cells, 1e4 of whose 5.4e5 slots each are taken, 16.1 -> 11.1 us.
+// us, 7e5 11.9 -> 9.5.  step_route.h says which tubes and batches take them, by the
+// slots that they are expected to hold, not by their capacity: eight cold tubes of
+// 11,036 cells, 1e4 of whose 5.4e5 slots each are taken, 16.1 -> 11.1 us.
 #include <math.h>
 
 #include "field_body.h"
@@ -244,14 +242,6 @@ __global__ __launch_bounds__(STEP_BLOCK) void k_batch_step(BatchRunArgs r)
                    J, ctr, &sc->w0[r.w_add], cnt, prev};
         push_tile_f64<STEP_BLOCK, 2, 1, 0, PART == 1>(c, a, n, tile0);
     }
-}
-
-// Slots that a tube is expected to fill: twice its particles at the corotation
-// density, as far as its capacity goes.
-int64_t run_slots(const pic_params &p)
-{
-    const double e = 2.0 * p.ppc * (double)p.n_cells;
-    return e < (double)p.capacity ? (int64_t)e : p.capacity;
 }
 
 // Blocks of one tube of a batch in a run's kernels.

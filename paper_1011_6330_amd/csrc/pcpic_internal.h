@@ -84,10 +84,6 @@ constexpr int HI_GROUP = 1 << HI_GROUP_LOG2;
 // Steps per captured round of a tube that never sorts (even: the field and
 // current buffers end a round in the parity they started it in).
 constexpr int64_t GRAPH_ROUND = 32;
-// Expected slots (run_slots) up to which a tube (all tubes of a batch together) takes
-// fused steps (k_step.hip has the times on both sides of it); an adjoint run always does, as it
-// also saves a kernel per step there that notes the slot count.
-constexpr int64_t FUSE_SLOTS = (int64_t)1 << 22;
 
 // Faces per thread of the field update (field_body.h): a wave takes 256 faces,
 // as two pairs per lane where the flat update applies.
@@ -354,6 +350,7 @@ struct pic_handle {
     int64_t mut = 0;    // changes of the tube's state other than steps (inject, load, field or schedule writes)
     AdjRecord adj;      // the last recorded adjoint forward
     std::atomic<int64_t> reads{0};   // diagnostics calls (a batch: of all its tubes)
+    std::atomic<int64_t> seen{0};    // occupied slots (both streams) when the host last saw them
     // batch (ensemble) handles
     bool is_batch = false;
     pic_handle *parent = nullptr;               // set on the tubes of a batch
@@ -372,7 +369,7 @@ struct pic_handle {
     int64_t batch_run_blocks = 0;               //   blocks of a kernel (0: the batch is too large for fused steps)
     int batch_block = 256, batch_ppt = 2;
     int64_t batch_push_items = 0, batch_field_items = 0, batch_sort_items = 0, batch_keys = 0, batch_scan_blocks = 0;
-    hipGraphExec_t graph[8] = {};   // one round, keyed by the (field, current, particle) buffer parities
+    hipGraphExec_t graph[16] = {};   // one round, keyed by the (field, current, particle) buffer parities and the kind of step
     bool use_graph = true;
 };
 
@@ -405,7 +402,6 @@ hipError_t launch_run(pic_handle *h, int64_t m, bool hist_last, int64_t *rec = n
 // The same for a batch; blocks of one of its tubes in a run's kernels.
 hipError_t launch_batch_run(pic_handle *h, int64_t m, bool hist_last);
 int64_t run_blocks(const pic_params &p);
-int64_t run_slots(const pic_params &p);
 // Current buffers of a run of m steps: step s (0: the one before the first, m + 1: the
 // one after the last) adds to run_j(jb, m, s).  Before and after a run they stand as
 // single steps leave them, since steps captured into a caller's graph hold the buffers

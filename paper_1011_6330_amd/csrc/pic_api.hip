@@ -352,6 +352,7 @@ pic_status read_counters(pic_handle *h, DevCounters *out)
     HIP_OK(hipStreamSynchronize(h->stream));
     st.idle = true;
     if (st.b.p) memcpy(out, dst, sizeof(DevCounters));
+    h->seen = out->n_slots + out->n_slots_hi;
     return PIC_OK;
 }
 
@@ -514,6 +515,7 @@ pic_status pic_inject(pic_handle *h, int64_t n, const double *x, const double *u
             }
             HIP_OK(launch_append_staged(h, m, false));
         }
+        h->seen += n;
         if (h->step == 0) {
             if (h->parent) h->poisson_pending = true;   // solved with the batch's other tubes
             else HIP_OK(launch_poisson(h));
@@ -549,8 +551,17 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
 static pic_status batch_status(pic_handle *h);
 static void free_batch_graphs(pic_handle *h);
 
-// Small tubes take their steps in fused runs (k_step.hip).
-static bool fused(const pic_handle *h) { return run_slots(h->p) <= FUSE_SLOTS && !(h->c.flags & PIC_GR_ALPHA); }
+static int64_t tube_slots(const pic_handle *t) { return expected_slots(t->p.ppc, t->p.n_cells, t->p.capacity, t->seen); }
+
+// Small tubes and batches take their steps in fused runs (step_route.h).
+static bool fused(const pic_handle *h)
+{
+    if (h->is_batch ? h->batch_run_blocks == 0 : (h->c.flags & PIC_GR_ALPHA) != 0) return false;
+    const bool f32 = (h->is_batch ? h->tubes[0] : h)->p.precision == PIC_FP32_BULK;
+    int64_t slots = h->is_batch ? 0 : tube_slots(h);
+    for (const pic_handle *t : h->tubes) slots += tube_slots(t);
+    return slots <= fuse_slots(h->is_batch, f32);
+}
 
 // The caller is capturing the stream into a graph: what is enqueued runs at that
 // graph's replays, and not now.
@@ -613,7 +624,7 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
     if (h->is_batch) return batch_advance(h, n_steps);
     // A whole round of sort_every steps that starts on a round boundary is
     // replayed from a graph captured once per (field, current, particle)
-    // buffer-parity state; other steps are launched one by one.  Both issue the
+    // buffer-parity state and kind of step; other steps are launched one by one.  Both issue the
     // same kernels with the same arguments.  A tube that never sorts takes
     // rounds of GRAPH_ROUND steps the same way (an even count, so a round ends
     // in the parity state it started from).
@@ -622,7 +633,7 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
     const bool in_capture = captured(h);
     while (n_steps > 0) {
         if (S > 1 && h->use_graph && !in_capture && h->step % S == 0 && n_steps >= S) {
-            const int key = h->fbuf | (h->jbuf << 1) | (h->pbuf << 2);
+            const int key = h->fbuf | (h->jbuf << 1) | (h->pbuf << 2) | (fused(h) ? 8 : 0);
             if (sorts) HIP_OK(launch_clear_hist(h));   // no part of the captured round
             if (!h->graph[key]) {
                 const int fb = h->fbuf, jb = h->jbuf, pb = h->pbuf;
@@ -931,6 +942,7 @@ pic_status pic_diagnostics(pic_handle *h, const pic_diag_req *req, pic_diag *out
         for (int k = 0; k < pk.n; ++k) memcpy(packed[k].dst, (char *)st.b.p + pk.seg[k].at * 8, packed[k].bytes);
     out->step = ctr.step;
     out->n_slots = ctr.n_slots + ctr.n_slots_hi;
+    h->seen = out->n_slots;
     out->n_alive = ctr.n_slots + ctr.n_slots_hi - ctr.n_removed;
     out->n_slots_high = ctr.n_slots_hi;
     out->n_injected = ctr.n_injected;
@@ -1299,6 +1311,7 @@ pic_status pic_load(pic_handle *h, const void *buf, size_t bytes)
     HIP_OK(hipMemcpyAsync(w.ctr, &ctr, sizeof ctr, hipMemcpyHostToDevice, h->stream));
     HIP_OK(launch_kick(h));
     HIP_OK(hipStreamSynchronize(h->stream));
+    h->seen = hd.n_lo + hd.n_hi;
     h->step = hd.step;
     return PIC_OK;
 }
@@ -1354,9 +1367,9 @@ static BatchMapSizes batch_map_sizes(const pic_params *tubes, int n)
         m.chunk += (p.capacity + SORT_TILE - 1) / SORT_TILE + (f32 ? 1 : 0);
         const int64_t keys = (f32 ? 2 * (p.n_cells + 1) : p.n_cells) << sort_sub_log2(p);
         m.scan += (keys + SORT_SCAN_TILE - 1) / SORT_SCAN_TILE;
-        slots += run_slots(p);
+        slots += expected_slots(p.ppc, p.n_cells, p.capacity, 0);
     }
-    if (slots <= FUSE_SLOTS)
+    if (slots <= fuse_slots(true, tubes[0].precision == PIC_FP32_BULK))
         for (int t = 0; t < n; ++t) m.run += run_blocks(tubes[t]);
     return m;
 }
@@ -1581,7 +1594,7 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
     if (pic_status sp = batch_resolve_pending(h)) return sp;
     pic_handle *t0 = h->tubes[0];
     const int64_t S = t0->p.sort_every;
-    const bool in_capture = captured(h);
+    const bool in_capture = captured(h), fuse = fused(h);
     while (n > 0) {
         int64_t r;
         if (S > 0) {
@@ -1591,8 +1604,8 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
             r = n < 64 ? n : 64;
         }
         const bool to_sort = S > 0 && (t0->step + r) % S == 0;
-        const bool run = h->batch_run_blocks > 0 && r > 1 && !ev;   // fused steps (timed runs measure push and field apart)
-        const int key = t0->fbuf | (t0->jbuf << 1) | (t0->pbuf << 2);
+        const bool run = fuse && r > 1 && !ev;   // timed runs measure push and field apart
+        const int key = t0->fbuf | (t0->jbuf << 1) | (t0->pbuf << 2) | (run ? 8 : 0);
         const bool round = to_sort && r == S && h->use_graph && !ev && !in_capture;
         const bool clear = h->counts_clear;
         if (to_sort && in_capture) h->counts_clear = false;   // as in tube_steps_direct

@@ -6,6 +6,33 @@
 
 namespace pcpic {
 
+// Slots up to which a tube, or all tubes of a batch together, take fused steps; past
+// them, forming the kicks per wave costs more than a kernel.  Per step, push and field
+// kernels against fused, ordered beams: FP64 of 16,384 cells 7e5 particles 11.9 / 9.5 us,
+// 1.2e6 14.8 / 13.3, 1.8e6 18.5 / 18.7, 2.5e6 22.0 / 24.2, of 65,536 cells 7e5 11.1 /
+// 10.0, 1.2e6 14.4 / 14.6, 1.8e6 17.4 / 18.4; FP32-bulk of 65,536 cells 1.2e6 14.2 / 12.7,
+// 1.5e6 14.6 / 13.9, 2.1e6 17.6 / 18.3; batches of eight (three kernels when not fused) FP64 of
+// 10,000 cells 2.4e6 30.2 / 27.4, 4e6 39.2 / 38.7, 6e6 50.8 / 54.2, FP32-bulk 4e6 36.0 /
+// 33.8.  An adjoint run always takes fused steps, as it also saves a kernel per step
+// there that notes the slot count.
+constexpr int64_t fuse_slots(bool batch, bool f32)
+{
+    return batch ? (int64_t)1 << 22 : (f32 ? (int64_t)1 << 21 : (int64_t)3 << 19);
+}
+
+// Slots that a tube is expected to hold: twice its particles at the corotation density,
+// as far as its capacity goes, or those it held when the host last saw their count
+// (loading, read-outs, pic_sync), if these are more.  (By the density alone, a tube of
+// 20,000 cells and ppc 20 took fused steps whatever it was loaded with: 1.2e7 particles
+// 116.9 us a step against 108.6 in separate kernels, 3e7 302.7 against 268.0; a batch
+// of eight with 3e6 each 195.0 against 180.4.)
+inline int64_t expected_slots(double ppc, int64_t n_cells, int64_t capacity, int64_t seen)
+{
+    const double e = 2.0 * ppc * (double)n_cells;
+    const int64_t slots = e < (double)capacity ? (int64_t)e : capacity;
+    return seen > slots ? seen : slots;
+}
+
 // Order of a single tube's push over its slots: ascending and descending in turn.  What
 // one step touched last the next touches first, while it is still in the 256 MiB
 // last-level cache.  Blocks go to the 8 XCDs in turn, each with an L2 of 4 MiB: the

@@ -51,3 +51,17 @@ def test_push_access_rule(tmp_path):
     CHECK(!push_nontemporal((int64_t)1 << 30) && push_nontemporal(((int64_t)1 << 30) + 1));
     CHECK(push_nontemporal(((int64_t)1 << 62)));
 """)
+
+
+@needs_gxx
+def test_expected_slots(tmp_path):
+    """The density's, the capacity's or the slots last seen, whichever decides."""
+    _run(tmp_path, """
+    CHECK(expected_slots(20.0, 20000, 14000000, 0) == 800000);
+    CHECK(expected_slots(20.0, 20000, 500000, 0) == 500000);
+    CHECK(expected_slots(20.0, 20000, 14000000, 12000000) == 12000000);
+    CHECK(expected_slots(20.0, 20000, 14000000, 700000) == 800000);
+    CHECK(expected_slots(1e300, 20000, 4096, 0) == 4096);
+    CHECK(expected_slots(20.0, 20000, 14000000, 12000000) > fuse_slots(true, false));
+    CHECK(fuse_slots(false, false) < fuse_slots(false, true) && fuse_slots(false, true) < fuse_slots(true, true));
+""")
