@@ -264,7 +264,7 @@ Workspace carve(const pic_params &p, uint8_t *base)
     w.rhs = (double *)take((N + 1) * 8);
     w.knots = (double *)take((size_t)(p.n_knots > 0 ? p.n_knots : 1) * 8);
     w.ctr = (DevCounters *)take(sizeof(DevCounters));
-    w.sc = (StepScratch *)take(sizeof(StepScratch));
+    w.sc = (StepScratch *)take(sizeof(StepScratch));   // behind the counters (COUNTERS_BYTES)
     w.pcount = (long long *)take(nb * 8);
     w.plo = (unsigned long long *)take(nb * 8);
     w.phi128 = (long long *)take(nb * 8);
@@ -440,8 +440,7 @@ static pic_status init_tube(const pic_params *p, void *d_workspace, size_t ws_by
         delete h;
         return fail(PIC_EDEVICE, "%s: %s", what, hipGetErrorString(e));
     };
-    hipError_t e = hipMemsetAsync(h->ws.ctr, 0, sizeof(DevCounters), h->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(h->ws.sc, 0, sizeof(StepScratch), h->stream);
+    hipError_t e = hipMemsetAsync(h->ws.ctr, 0, COUNTERS_BYTES, h->stream);
     if (e != hipSuccess) return bail(e, "clear counters");
     if (!h->knots.empty()) {
         e = hipMemcpyAsync(h->ws.knots, h->knots.data(), h->knots.size() * 8, hipMemcpyHostToDevice, h->stream);
