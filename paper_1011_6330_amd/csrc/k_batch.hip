@@ -139,7 +139,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_field(BatchArgs b)
 struct BSortArgs {
     const TubeDev *tubes;
     int n_tubes;
-    const int64_t *chunk_pref;   // [n_tubes + 1] prefix of sort items (tiles of SORT_TILE slots, sort_item)
+    const int64_t *chunk_pref;   // [n_tubes + 1] prefix of sort items (tiles of SORT_TILE slots, sort_item; scatter_blocks)
     const int64_t *key_pref;     // [n_tubes + 1] prefix of sort keys
     const int64_t *scan_pref;    // [n_tubes + 1] prefix of scan blocks
     const int32_t *chunk_map;    // sort chunk -> tube

@@ -211,13 +211,12 @@ hipError_t launch_push_f32(pic_handle *h)
     return hipErrorInvalidValue;
 }
 
-// Blocks of a pass over both streams in tiles of SORT_TILE slots (sort_item).
-static unsigned sort_items32(pic_handle *h) { return (unsigned)((h->c.cap + SORT_TILE - 1) / SORT_TILE + 1); }
-
 hipError_t launch_sort32_scatter(pic_handle *h, int64_t n_keys)
 {
     const int src = h->pbuf, dst = 1 - h->pbuf;
-    hipLaunchKernelGGL(k_scatter32, dim3(sort_items32(h)), dim3(SORT_BLOCK), 0, h->stream, h->c, streams_of(h, src),
+    // tiles of both streams, any split (sort_item)
+    const unsigned blocks = (unsigned)scatter_blocks((h->c.cap + SORT_TILE - 1) / SORT_TILE + 1, n_keys);
+    hipLaunchKernelGGL(k_scatter32, dim3(blocks), dim3(SORT_BLOCK), 0, h->stream, h->c, streams_of(h, src),
                        streams_of(h, dst), h->ws.ctr, h->ws.sc, h->u_hi, (unsigned long long *)h->ws.cell_off,
                        (const long long *)h->ws.total_lo, h->ws.cell_count, n_keys);
     return hipGetLastError();

@@ -83,8 +83,8 @@ hipError_t launch_sort(pic_handle *h)
     if (f32) {
         e = launch_sort32_scatter(h, nkeys);
     } else {
-        const unsigned tiles = (unsigned)((c.cap + SORT_TILE - 1) / SORT_TILE);
-        hipLaunchKernelGGL(k_scatter, dim3(tiles), dim3(SORT_BLOCK), 0, h->stream, c, w.x[src], w.u[src], w.x[dst],
+        const unsigned blocks = (unsigned)scatter_blocks((c.cap + SORT_TILE - 1) / SORT_TILE, nkeys);
+        hipLaunchKernelGGL(k_scatter, dim3(blocks), dim3(SORT_BLOCK), 0, h->stream, c, w.x[src], w.u[src], w.x[dst],
                            w.u[dst], w.ctr, w.sc, (unsigned long long *)w.cell_off, w.cell_count, nkeys);
         e = hipGetLastError();
     }

@@ -1363,8 +1363,8 @@ static BatchMapSizes batch_map_sizes(const pic_params *tubes, int n)
         const bool f32 = p.precision == PIC_FP32_BULK;
         m.push += (p.capacity + 127) / 128 + 2;
         m.field += (p.n_cells + 63) / 64;
-        m.chunk += (p.capacity + SORT_TILE - 1) / SORT_TILE + (f32 ? 1 : 0);
         const int64_t keys = (f32 ? 2 * (p.n_cells + 1) : p.n_cells) << sort_sub_log2(p);
+        m.chunk += scatter_blocks((p.capacity + SORT_TILE - 1) / SORT_TILE + (f32 ? 1 : 0), keys);
         m.scan += (keys + SORT_SCAN_TILE - 1) / SORT_SCAN_TILE;
         slots += expected_slots(p.ppc, p.n_cells, p.capacity, 0);
     }
@@ -1438,7 +1438,8 @@ static pic_status batch_configure(pic_handle *h, int block, int per_thread)
         td[(size_t)t].push_tiles_hi = f32 ? 1 : 0;
         pp[(size_t)t + 1] = pp[(size_t)t] + td[(size_t)t].push_tiles + td[(size_t)t].push_tiles_hi;
         fp[(size_t)t + 1] = fp[(size_t)t] + (s->c.N + block * FIELD_CPT - 1) / (block * FIELD_CPT);
-        sp[(size_t)t + 1] = sp[(size_t)t] + td[(size_t)t].sort_chunks + (f32 ? 1 : 0);   // sort_item
+        sp[(size_t)t + 1] = sp[(size_t)t] + scatter_blocks(td[(size_t)t].sort_chunks + (f32 ? 1 : 0),   // sort_item
+                                                           td[(size_t)t].n_keys);
         kp[(size_t)t + 1] = kp[(size_t)t] + td[(size_t)t].n_keys;
         cp[(size_t)t + 1] = cp[(size_t)t] + (td[(size_t)t].n_keys + SORT_SCAN_TILE - 1) / SORT_SCAN_TILE;
     }

@@ -86,3 +86,33 @@ def test_sorts_of_a_batch(precision, sizes):
     _check(bs[0].tubes, bs[1].tubes, lambda M: [b.step(M) for b in bs], precision == 1, 8.0)
     for b in bs:
         b.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n_cells,capacity", [(8192, 100), (8193, 1024), (70001, 1025), (300000, 900)])
+def test_more_keys_than_the_slots_blocks_clear(n_cells, capacity, precision):
+    """Tubes of many keys and few slots, whose scatter has blocks that only clear counts: alone
+    and in a batch, against a tube that never sorts."""
+    from paper_1011_6330_amd import Batch, Tube
+    cfg = dict(synth.preset("c1"), n_cells=n_cells, length=1e-3 * n_cells, ppc=1e-3, capacity=capacity, flags=1,
+               precision=precision, gamma_fp64=8.0)
+    x, u = synth.random_particles(n_cells, min(capacity, 80), seed=9)
+    plain, alone = Tube(synth.tube_params(cfg)), Tube(synth.tube_params(dict(cfg, sort_every=2)))
+    b = Batch([synth.tube_params(dict(cfg, sort_every=2)), synth.tube_params(dict(cfg, sort_every=2, n_cells=50))])
+    for t in (plain, alone, b.tubes[0]):
+        t.inject(x, u)
+    for h in (plain, alone, b):
+        h.step(9)
+
+    def state(t):
+        d = t.diagnostics(n_bins=8, fields=True, j=True)
+        px, pu = t.read_particles()
+        k = np.lexsort((pu, px))
+        return [d["ez"], d["er"], d["b_phi"], d["j_last"], d["prof_count"], px[k], pu[k]]
+
+    want = state(plain)
+    for t in (alone, b.tubes[0]):
+        for a, c in zip(want, state(t)):
+            assert np.array_equal(a, c)
+    for h in (plain, alone, b):
+        h.close()

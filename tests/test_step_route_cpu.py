@@ -65,3 +65,12 @@ def test_expected_slots(tmp_path):
     CHECK(expected_slots(20.0, 20000, 14000000, 12000000) > fuse_slots(true, false));
     CHECK(fuse_slots(false, false) < fuse_slots(false, true) && fuse_slots(false, true) < fuse_slots(true, true));
 """)
+
+
+@needs_gxx
+def test_scatter_blocks(tmp_path):
+    """The tiles' blocks, unless the key counts need more to be cleared 2048 to a block."""
+    _run(tmp_path, """
+    CHECK(scatter_blocks(4, 2048) == 4 && scatter_blocks(4, 4 * 2048) == 4 && scatter_blocks(4, 4 * 2048 + 1) == 5);
+    CHECK(scatter_blocks(1, 1 << 20) == 512 && scatter_blocks(40000, 1 << 20) == 40000);
+""")
