@@ -167,14 +167,17 @@ __global__ __launch_bounds__(256) void k_kick(Consts c, const double *ez, float 
 
 // Check appended particles in slots [base, base + n): 0 <= x < N and u finite.
 __global__ __launch_bounds__(256) void k_check_append(Consts c, const double *X, const double *U, int64_t base,
-                                                      int64_t n, DevCounters *ctr)
+                                                      int64_t n, DevCounters *ctr, int64_t *jumps, int stride)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     bool bad = false;
+    int cell = -1;
     if (i < n) {
         const double x = X[base + i], u = U[base + i];
         bad = !(x >= 0.0 && x < (double)c.N) || !isfinite(u);
+        if (!bad) cell = (int)x;
     }
+    count_jumps(cell, 128, stride, jumps);
     const int64_t nb = wave_sum_i64(bad ? 1 : 0);
     if (__lane_id() == 0 && nb) atomicAdd((unsigned long long *)&ctr->bad_inputs, (unsigned long long)nb);
 }
@@ -277,7 +280,7 @@ hipError_t launch_check_append(pic_handle *h, int64_t base, int64_t n)
 {
     if (n > 0)
         hipLaunchKernelGGL(k_check_append, dim3(grid_for(n, 256)), dim3(256), 0, h->stream, h->c,
-                           h->ws.x[h->pbuf], h->ws.u[h->pbuf], base, n, h->ws.ctr);
+                           h->ws.x[h->pbuf], h->ws.u[h->pbuf], base, n, h->ws.ctr, &h->ws.sc->jumps, (int)jump_stride(n));
     return hipGetLastError();
 }
 

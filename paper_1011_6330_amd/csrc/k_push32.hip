@@ -57,13 +57,14 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_scatter32(Consts c, Streams src,
         scatter_tile_f32<false>(c, src, dst, u_hi, tlo, off, n, tile0);
 }
 
-// Staged particles (x in cell units, u) -> validity count.
+// Staged particles (x in cell units, u) -> validity count, and their jumps.
 __global__ __launch_bounds__(256) void k_check_staged(Consts c, const double *X, const double *U, int64_t n,
-                                                      DevCounters *ctr)
+                                                      DevCounters *ctr, int64_t *jumps, int stride)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     bool bad = false;
     if (i < n) bad = !(X[i] >= 0.0 && X[i] < (double)c.N) || !isfinite(U[i]);
+    count_jumps(i < n && !bad ? (int)X[i] : -1, 256, stride, jumps);
     const int64_t nb = wave_sum_i64(bad ? 1 : 0);
     if (__lane_id() == 0 && nb) atomicAdd((unsigned long long *)&ctr->bad_inputs, (unsigned long long)nb);
 }
@@ -227,7 +228,7 @@ hipError_t launch_append_staged(pic_handle *h, int64_t n, bool check_only)
     const unsigned g = (unsigned)((n + 255) / 256);
     if (check_only) {
         hipLaunchKernelGGL(k_check_staged, dim3(g), dim3(256), 0, h->stream, h->c, h->ws.stage_x, h->ws.stage_u, n,
-                           h->ws.ctr);
+                           h->ws.ctr, &h->ws.sc->jumps, (int)jump_stride(n));
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_stage_count, dim3(g), dim3(256), 0, h->stream, h->ws.stage_u, n, h->u_hi, h->ws.stage_blk);

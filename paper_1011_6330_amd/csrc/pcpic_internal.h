@@ -176,10 +176,12 @@ struct DevCounters {
 // that the pushes of a step take (two words in turn) and the node-0 tallies of
 // three steps in turn (all zero between runs).  sort_n: the slots of the two streams
 // that a sort reads, kept for its scatter, which sets the counters to the new ones.
+// jumps: jumps (step_route.h) counted in all slots loaded so far; only ever grows.
 struct StepScratch {
     int64_t n[2];
     unsigned long long w0[3];
     int64_t sort_n[2];
+    int64_t jumps;
 };
 // The two follow each other in the workspace and are cleared together: a whole number of
 // 16-byte words, which the runtime fills with one kernel.  (Cleared one by one, with 56
@@ -357,6 +359,8 @@ struct pic_handle {
     AdjRecord adj;      // the last recorded adjoint forward
     std::atomic<int64_t> reads{0};   // diagnostics calls (a batch: of all its tubes)
     std::atomic<int64_t> seen{0};    // occupied slots (both streams) when the host last saw them
+    int64_t jumps = -1;              // jumps (step_route.h) among the slots, -1: they are in order
+    int64_t jumps_counted = 0;       // the device's count after the last load
     // batch (ensemble) handles
     bool is_batch = false;
     pic_handle *parent = nullptr;               // set on the tubes of a batch

@@ -1,8 +1,10 @@
 // pic_api.hip -- host side of the C ABI declared in include/pcpic.h:
 // parameter validation, workspace carve-up, the per-step launch sequence and
 // the synchronising read-back calls.  No device memory is ever allocated here.
+#include <limits.h>
 #include <math.h>
 #include <stdarg.h>
+#include <stddef.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -343,15 +345,19 @@ pic_status write_high_stream(pic_handle *h, int b, int64_t ns, const int *cell, 
     return PIC_OK;
 }
 
-pic_status read_counters(pic_handle *h, DevCounters *out)
+// jumps (or null): also the jumps counted in the slots loaded so far.
+pic_status read_counters(pic_handle *h, DevCounters *out, int64_t *jumps = nullptr)
 {
-    Pinned st(sizeof(DevCounters), h->stream, false);
-    void *dst = st.b.p ? st.b.p : out;
+    alignas(16) uint8_t own[COUNTERS_BYTES];
+    const size_t bytes = jumps ? COUNTERS_BYTES : sizeof(DevCounters);
+    Pinned st(bytes, h->stream, false);
+    void *dst = st.b.p ? st.b.p : own;
     st.idle = false;
-    HIP_OK(hipMemcpyAsync(dst, h->ws.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost, h->stream));
+    HIP_OK(hipMemcpyAsync(dst, h->ws.ctr, bytes, hipMemcpyDeviceToHost, h->stream));
     HIP_OK(hipStreamSynchronize(h->stream));
     st.idle = true;
-    if (st.b.p) memcpy(out, dst, sizeof(DevCounters));
+    memcpy(out, dst, sizeof(DevCounters));
+    if (jumps) memcpy(jumps, (uint8_t *)dst + 256 + offsetof(StepScratch, jumps), sizeof *jumps);
     h->seen = out->n_slots + out->n_slots_hi;
     return PIC_OK;
 }
@@ -360,6 +366,33 @@ double i128_to_double(unsigned long long lo, long long hi)
 {
     const __int128 v = ((__int128)hi << 64) | (__int128)lo;
     return (double)v;
+}
+
+// The counters after a load's check, whose jumps are added to those of the slots.
+pic_status read_loaded(pic_handle *h, DevCounters *out)
+{
+    int64_t jumps = 0;
+    if (pic_status s = read_counters(h, out, &jumps)) return s;
+    if (!out->bad_inputs) h->jumps = (h->jumps > 0 ? h->jumps : 0) + (jumps - h->jumps_counted);
+    h->jumps_counted = jumps;
+    return PIC_OK;
+}
+
+// The jumps among n slots on the host, counted as count_jumps does; cell(i) < 0: none.
+template <class F>
+int64_t host_jumps(int64_t n, int wave, F cell)
+{
+    const int64_t stride = jump_stride(n);
+    int64_t sum = 0;
+    for (int64_t g = 0; g < n; g += 256 * stride)
+        for (int64_t w = g; w < n && w < g + 256; w += wave) {
+            const int64_t e = w + wave < n ? w + wave : n;
+            int lo = INT_MAX;
+            for (int64_t i = w; i < e; ++i) lo = cell(i) >= 0 && cell(i) < lo ? cell(i) : lo;
+            for (int64_t i = w + 1; i < e; ++i)
+                sum += cell(i) >= 0 && cell(i) - lo > 62 && (cell(i) >> 3) != (cell(i - 1) >> 3);
+        }
+    return sum * stride;
 }
 
 // Every particle finite and inside [0, N); without branches, so that the loop is
@@ -502,7 +535,7 @@ pic_status pic_inject(pic_handle *h, int64_t n, const double *x, const double *u
             HIP_OK(hipMemcpyAsync(h->ws.stage_u, u + o, (size_t)m * 8, kind, h->stream));
             HIP_OK(launch_append_staged(h, m, true));
         }
-        s = read_counters(h, &ctr);
+        s = read_loaded(h, &ctr);
         if (s != PIC_OK) return s;
         if (ctr.bad_inputs)
             return fail(PIC_EINVAL, "%lld particles outside [0, N) or not finite", (long long)ctr.bad_inputs);
@@ -531,7 +564,7 @@ pic_status pic_inject(pic_handle *h, int64_t n, const double *x, const double *u
     HIP_OK(hipMemsetAsync(&h->ws.ctr->bad_inputs, 0, sizeof(int64_t), h->stream));
     HIP_OK(launch_check_append(h, ctr.n_slots, n));
     HIP_OK(launch_commit_append(h, n));
-    s = read_counters(h, &ctr);
+    s = read_loaded(h, &ctr);
     if (s != PIC_OK) return s;
     if (ctr.bad_inputs) return fail(PIC_EINVAL, "%lld particles outside [0, N) or not finite", (long long)ctr.bad_inputs);
     if (h->step == 0) {
@@ -552,6 +585,21 @@ static void free_batch_graphs(pic_handle *h);
 
 static int64_t tube_slots(const pic_handle *t) { return expected_slots(t->p.ppc, t->p.n_cells, t->p.capacity, t->seen); }
 
+// Jumps among a tube's slots: those of its loaded particles, or those that particles in
+// order have at the corotation density; and what a sort leaves of them.
+static int64_t tube_jumps(const pic_handle *t)
+{
+    if (t->jumps >= 0) return t->jumps;
+    const double e = t->p.ppc * (double)t->p.n_cells;
+    return ordered_jumps(e < (double)t->c.cap ? (int64_t)e : t->c.cap, t->c.N, t->p.precision == PIC_FP32_BULK);
+}
+static void jumps_sorted(pic_handle *t)
+{
+    if (t->jumps <= 0) return;
+    const int64_t left = ordered_jumps(t->seen, t->c.N, t->p.precision == PIC_FP32_BULK);
+    if (left < t->jumps) t->jumps = left;
+}
+
 // Small tubes and batches take their steps in fused runs (step_route.h).
 static bool fused(const pic_handle *h)
 {
@@ -559,7 +607,14 @@ static bool fused(const pic_handle *h)
     const bool f32 = (h->is_batch ? h->tubes[0] : h)->p.precision == PIC_FP32_BULK;
     int64_t slots = h->is_batch ? 0 : tube_slots(h);
     for (const pic_handle *t : h->tubes) slots += tube_slots(t);
-    return slots <= fuse_slots(h->is_batch, f32);
+    if (slots > fuse_slots(h->is_batch, f32)) return false;
+    if (!h->is_batch) {
+        const int64_t j = tube_jumps(h), n = h->jumps >= 0 ? (int64_t)h->seen : slots;
+        return j <= most_jumps(j, n, h->c.N, f32);
+    }
+    double share = 0.0;
+    for (const pic_handle *t : h->tubes) share += (double)tube_jumps(t) / (double)most_jumps_batch(t->c.N);
+    return share <= 1.0;
 }
 
 // The caller is capturing the stream into a graph: what is enqueued runs at that
@@ -602,6 +657,7 @@ static pic_status tube_steps_direct(pic_handle *h, int64_t m, bool in_capture = 
     if (sort_after) {
         HIP_OK(launch_sort(h));
         if (in_capture) h->counts_clear = clear;
+        else jumps_sorted(h);
     }
     return PIC_OK;
 }
@@ -661,7 +717,10 @@ pic_status pic_step(pic_handle *h, int64_t n_steps)
             HIP_OK(hipGraphLaunch(h->graph[key], h->stream));
             h->fbuf ^= (int)(S & 1);
             h->jbuf ^= (int)(S & 1);
-            if (sorts) h->pbuf ^= 1;
+            if (sorts) {
+                h->pbuf ^= 1;
+                jumps_sorted(h);
+            }
             h->step += S;
             n_steps -= S;
         } else {
@@ -745,6 +804,7 @@ pic_status pic_step_timed(pic_handle *h, int64_t n_steps, pic_timing *out)
         h->step += 1;
         const bool sorted = sort_after;
         if (sort_after && launch_sort(h) != hipSuccess) { rc = fail(PIC_EDEVICE, "sort launch failed"); break; }
+        if (sort_after) jumps_sorted(h);
         if (hipEventRecord(e[3], h->stream) != hipSuccess) { rc = fail(PIC_EDEVICE, "event record failed"); break; }
         slots_before[(size_t)s] = sorted ? -1 : 0;
     }
@@ -1311,6 +1371,20 @@ pic_status pic_load(pic_handle *h, const void *buf, size_t bytes)
     HIP_OK(launch_kick(h));
     HIP_OK(hipStreamSynchronize(h->stream));
     h->seen = hd.n_lo + hd.n_hi;
+    auto cell32 = [&](size_t at) {
+        return [&in, at](int64_t i) {
+            int c;
+            memcpy(&c, in + at + 4 * (size_t)i, 4);
+            return c;
+        };
+    };
+    auto cell64 = [&](int64_t i) {
+        double x;
+        memcpy(&x, in + L.p[0] + 8 * (size_t)i, 8);
+        return x >= 0.0 ? (int)x : -1;
+    };
+    h->jumps = f32 ? host_jumps(hd.n_lo, 256, cell32(L.p[0])) + host_jumps(hd.n_hi, 256, cell32(L.p[3]))
+                   : host_jumps(hd.n_lo, 128, cell64);
     h->step = hd.step;
     return PIC_OK;
 }
@@ -1661,6 +1735,7 @@ static pic_status batch_advance(pic_handle *h, int64_t n, std::vector<hipEvent_t
             t->jbuf ^= (int)(r & 1);
             t->step += r;
             if (to_sort) t->pbuf ^= 1;
+            if (to_sort && !in_capture) jumps_sorted(t);
         }
         n -= r;
     }

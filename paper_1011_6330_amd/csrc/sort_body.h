@@ -13,6 +13,7 @@
 // velocities, in the same wave.
 #pragma once
 
+#include <limits.h>
 #include <math.h>
 
 #include "pcpic_internal.h"
@@ -50,6 +51,26 @@ __device__ __forceinline__ void hi_put_wide(const Streams &s, int64_t q, int cel
     s.HP[q] = frac;
     s.UH[q] = u;
     if ((q & (HI_GROUP - 1)) == 0) s.HG[q >> HI_GROUP_LOG2] = HI_WIDE;
+}
+
+// Adds to *jumps the jumps (step_route.h) among the loaded particles of this block of 256,
+// one per thread, cell < 0 for none, waves of the push taking `wave` of them; a block
+// stands for `stride` of them, and the others return at once.  Called by every thread.
+__device__ __forceinline__ void count_jumps(int cell, int wave, int stride, int64_t *jumps)
+{
+    if (blockIdx.x % (unsigned)stride != 0) return;
+    __shared__ int s_lo[4], s_n;
+    const int w = threadIdx.x >> 6;
+    const int lo1 = wave_min_i32(cell >= 0 ? cell : INT_MAX);
+    if (threadIdx.x == 0) s_n = 0;
+    if (__lane_id() == 0) s_lo[w] = lo1;
+    __syncthreads();
+    const int lo2 = min(s_lo[w], s_lo[w ^ 1]), lo = wave == 256 ? min(lo2, min(s_lo[w ^ 2], s_lo[w ^ 3])) : lo2;
+    const int before = __shfl_up(cell, 1);
+    const unsigned long long m = __ballot(cell >= 0 && cell - lo > 62 && (cell >> 3) != (before >> 3));
+    if (__lane_id() == 0 && m) atomicAdd(&s_n, __popcll(m));
+    __syncthreads();
+    if (threadIdx.x == 0 && s_n) atomicAdd((unsigned long long *)jumps, (unsigned long long)s_n * (unsigned)stride);
 }
 
 // Destination stream of a particle: the high stream from |u| >= u_hi on.

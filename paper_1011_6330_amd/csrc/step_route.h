@@ -50,6 +50,48 @@ inline int64_t expected_slots(double ppc, int64_t n_cells, int64_t capacity, int
 constexpr int64_t CACHED_BYTES = (int64_t)1 << 30, L2_BYTES = (int64_t)32 << 20;
 constexpr bool push_nontemporal(int64_t bytes) { return bytes <= L2_BYTES || bytes > CACHED_BYTES; }
 
+// A fused step's push keeps the kicks at 64 faces per wave and forms those past them from
+// the fields, about ten words from four arrays where a separate push reads two.  A slot
+// more than 62 cells above the lowest of its wave's and not in the 8 cells of the slot
+// before it is a jump: a load of cache lines of its own.  Slots in order have them
+// where they are sparse (a wave takes 128 of them, 256 in FP32-bulk): `slots` spread
+// evenly over n_cells.
+inline int64_t ordered_jumps(int64_t slots, int64_t n_cells, bool f32)
+{
+    if (slots <= 0) return 0;
+    const double gap = (double)n_cells / (double)slots, span = (f32 ? 256.0 : 128.0) * gap;
+    return span > 63.0 ? (int64_t)((double)slots * (1.0 - 63.0 / span) * (gap < 8.0 ? gap / 8.0 : 1.0)) : 0;
+}
+
+// Jumps from which on a tube's steps are faster in separate kernels.  Per step, push and
+// field kernels against fused, shuffled slots: FP64 of 2,048 cells 1e5 18.9 / 17.1 us,
+// 4e5 54.1 / 55.8; of 10,000 cells 1e5 15.0 / 13.8, 4e5 39.3 / 43.3; of 65,536 cells 2e4
+// 8.3 / 9.1, 4e5 35.3 / 41.8; of 2^20 cells 2e5 30.4 / 45.7, 3e6 216 / 403; FP32-bulk of
+// 10,000 cells 2e4 10.6 / 10.5, 4e5 39.2 / 46.5; of 65,536 cells 2e4 9.9 / 12.4.  A tenth of the
+// slots shuffled, 65,536 cells: FP64 1e5 9.2 / 9.0, 1e6 19.9 / 22.4.  Sparse and in order:
+// FP64 of 65,536 cells 2e4 8.1 / 6.9, of 200,000 1e5 11.6 / 12.1, of 2^20 4e5 34.1 / 36.3,
+// FP32-bulk 42.6 / 50.5.
+inline int64_t most_jumps(int64_t jumps, int64_t slots, int64_t n_cells, bool f32)
+{
+    const bool most = 2 * jumps > slots;
+    if (n_cells < 4096) return 1 << 17;
+    if (n_cells < 32768) return f32 ? (most ? 1 << 10 : 1 << 16) : 1 << 17;
+    if (most) return f32 ? 1 << 10 : 1 << 12;
+    return n_cells < 131072 ? 1 << 13 : 1 << 12;
+}
+// The same for one tube of a batch, whose tubes hide each other's latencies and which
+// takes three kernels when not fused (eight shuffled tubes of 10,000 cells, FP64: 5,000
+// particles each 17.4 / 13.2, 50,000 43.3 / 43.9, 2e5 135.5 / 141.3; of 65,536 cells 5,000
+// 20.7 / 19.8, 50,000 48.7 / 57.2).
+constexpr int64_t most_jumps_batch(int64_t n_cells)
+{
+    return n_cells < 4096 ? 1 << 19 : (n_cells < 32768 ? 1 << 17 : 1 << 16);
+}
+
+// Sampling of the loaded slots in which jumps are counted: every jump_stride-th group of
+// 256, so that about 1024 groups add to the count.
+constexpr int64_t jump_stride(int64_t n) { return (n + 256 * 1024 - 1) / (256 * 1024); }
+
 // Blocks of a sort's scatter over `tiles` tiles of slots: they also clear the key counts,
 // so a tube of many keys and few slots gets blocks for these, 2048 keys each.  (Clearing
 // by 1 block instead of 512, 2^20 keys of a tube of 1,024 slots took 48.5 us a step with a

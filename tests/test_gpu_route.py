@@ -62,3 +62,43 @@ def test_route_changes_keep_the_bits(precision, sort_every, batch):
     _same(*tubes, "at the end")
     for h in hs:
         h.close()
+
+
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("sort_every", [0, 8])
+def test_scattered_slots_keep_the_bits(precision, sort_every, batch):
+    """Shuffled slots over many cells take separate kernels until a sort, a load of an ordered
+    beam goes on fused, a saved state is judged by its slots."""
+    from paper_1011_6330_amd import Batch, Tube
+    cells, n = 40000, 70000 if batch else 9000
+    p = synth.tube_params(dict(synth.preset("c1"), n_cells=cells, length=400.0, ppc=4.0, capacity=400000, flags=1,
+                               precision=precision, gamma_fp64=8.0, sort_every=sort_every))
+    x, u = synth.random_particles(cells, n, seed=4)
+    y, v = synth.random_particles(cells, 3000, seed=5)
+    order = np.argsort(y)
+    hs = [Batch([p, dict(p, n_cells=300, length=3.0)]) if batch else Tube(p) for _ in range(2)]
+    tubes = [h.tubes if batch else [h] for h in hs]
+    for t in tubes:
+        t[0].inject(x, u)
+    for m in (20, 7, 13):
+        hs[0].step(m)
+        for _ in range(m):
+            hs[1].step(1)
+        _same(*tubes, f"after {m} steps")
+        for t in tubes:
+            t[0].inject(y[order], v[order])
+    if not batch:
+        state = hs[0].save()
+        hs[0].load(state)
+        c = Tube(p)
+        c.load(state)
+        for _ in range(24):
+            hs[1].step(1)
+        hs[0].step(24)
+        c.step(24)
+        _same(*tubes, "after loading its own state")
+        _same([c], [hs[1]], "loaded into another tube")
+        c.close()
+    for h in hs:
+        h.close()

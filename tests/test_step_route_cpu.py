@@ -74,3 +74,28 @@ def test_scatter_blocks(tmp_path):
     CHECK(scatter_blocks(4, 2048) == 4 && scatter_blocks(4, 4 * 2048) == 4 && scatter_blocks(4, 4 * 2048 + 1) == 5);
     CHECK(scatter_blocks(1, 1 << 20) == 512 && scatter_blocks(40000, 1 << 20) == 40000);
 """)
+
+
+@needs_gxx
+def test_jump_rules(tmp_path):
+    """Slots in order have jumps only where a wave spans more than 63 cells; the limits fall
+    with the cells, and where most of the slots jump."""
+    _run(tmp_path, """
+    CHECK(ordered_jumps(0, 1000, false) == 0 && ordered_jumps(1000000, 65536, false) == 0);
+    CHECK(ordered_jumps(300000, 100000, true) > 0 && ordered_jumps(300000, 100000, false) == 0);
+    CHECK(ordered_jumps(20000, 65536, false) > 6000 && ordered_jumps(20000, 65536, false) < 8000);
+    CHECK(ordered_jumps(10, 1 << 20, false) <= 10);
+    CHECK(jump_stride(1) == 1 && jump_stride(256 * 1024) == 1 && jump_stride(256 * 1024 + 1) == 2);
+    for (int f32 = 0; f32 < 2; ++f32) {
+        int64_t last = INT64_MAX;
+        for (int64_t n : {700, 4095, 4096, 32767, 32768, 131071, 131072, 1 << 24}) {
+            const int64_t few = most_jumps(1000, 1000000, n, f32), most = most_jumps(1000000, 1000000, n, f32);
+            CHECK(most <= few && few <= last && most > 0);
+            last = few;
+        }
+    }
+    CHECK(400000 > most_jumps(400000, 400000, 65536, false));      // 35.3 us a step in separate kernels, 41.8 fused
+    CHECK(98000 <= most_jumps(98000, 100000, 10000, false));       // 15.0 / 13.8
+    CHECK(7000 <= most_jumps(7000, 20000, 65536, false));          // 8.1 / 6.9
+    CHECK(19800 > most_jumps(19800, 20000, 65536, true));          // 9.9 / 12.4
+""")
