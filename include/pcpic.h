@@ -227,6 +227,10 @@ pic_status pic_inject(pic_handle *h, int64_t n, const double *x, const double *u
 /* Enqueue n_steps PIC cycles on the stream and return.  Each cycle: push and
  * charge-conserving deposit, boundary removal, leap-frog field update, SCLF
  * injection; every sort_every cycles a cell sort that drops removed particles.
+ * Flat tubes of up to 1.6 million slots (FP32-bulk 2.1 million), expected at their
+ * density or seen by the host at the last load, read-out or sync, take calls of two
+ * steps and more in fused steps, one kernel each, unless their slots are scattered over
+ * many cells; other tubes a push and a field kernel per step.  The results are the same.
  * Kernels only, so the caller may capture it into a graph of its own; a graph of an
  * even number of steps (with a sort: an even number of whole sort periods, begun at
  * one) may be replayed again and again, with other such calls in between.
@@ -297,8 +301,9 @@ enum {
  * slots apart.  FP32-bulk: 4 (4 consecutive low-stream slots per thread; in
  * the high stream two pairs of slots 128 apart).  pic_init sets 128 x 2 (FP64) or
  * 128 x 4 (FP32-bulk), with PIC_PUSH_NONTEMPORAL where the particle streams at
- * capacity take up to 32 MiB or more than 1 GiB.  Tubes small enough for fused steps (k_step.hip)
- * have one shape of their own there.
+ * capacity take up to 32 MiB or more than 1 GiB.  The fused steps of smaller tubes
+ * (pic_step) have one shape of their own, and lapse tubes (PIC_GR_ALPHA) one with
+ * either access.
  * Results do not depend on the choice (integer deposition); the autotuner
  * picks the fastest.  Errors: PIC_EINVAL for an unsupported shape or flag. */
 pic_status pic_set_push_config(pic_handle *h, int32_t block, int32_t per_thread, uint32_t flags);
@@ -307,12 +312,11 @@ pic_status pic_set_push_config(pic_handle *h, int32_t block, int32_t per_thread,
  *
  * A batch holds n_tubes tubes of any sizes (each tube's parameters as for
  * pic_init; all tubes share the precision and sort_every).  pic_step on the
- * batch handle advances every tube.  A batch of up to 4.2 million expected slots takes
- * one kernel per step (the field update of the step before and the push); in a larger
- * one each step is a push kernel and a field
- * kernel over all tubes, over device lists of (tube, tile) work items, one
- * block per item.  No block waits for another;
- * the kernel boundary orders the phases.  Up to sort_every steps plus a batched
+ * batch handle advances every tube.  A batch of up to 4.2 million slots, expected or
+ * seen, takes one kernel per step (the field update of the step before and the push,
+ * as in pic_step); in a larger one each step is a push kernel and a field kernel over
+ * all tubes, over device lists of (tube, tile) work items, one block per item.  No
+ * block waits for another; the kernel boundary orders the phases.  Up to sort_every steps plus a batched
  * cell sort form a round, captured once in a HIP graph and replayed with one
  * launch.  A tube of a batch computes exactly what it computes when stepped
  * alone.  Before each push a one-block kernel lists the push items that hold
@@ -341,13 +345,14 @@ enum {
 };
 
 /* Launch shape of the batched kernels: threads per block (64..512) and slots
- * per thread (FP64: 2 or 4; FP32-bulk: 4).  Results do not depend on the
+ * per thread (FP64: 2 or 4; FP32-bulk: 4) of the separate push and field
+ * kernels; fused steps have one shape of their own.  Results do not depend on the
  * choice.  Errors: PIC_EINVAL for an unsupported shape or flag. */
 pic_status pic_batch_set_config(pic_handle *batch, int32_t block, int32_t per_thread, uint32_t flags);
 
 /* Current launch shape (any pointer may be NULL): threads per block, slots per
- * thread, and the blocks of one step's push and field kernels (one per tile of
- * every tube, particle tiles counted at capacity). */
+ * thread, and the blocks of one step's separate push and field kernels (one per
+ * tile of every tube, particle tiles counted at capacity). */
 pic_status pic_batch_get_config(pic_handle *batch, int32_t *block, int32_t *per_thread, int64_t *push_blocks,
                                 int64_t *field_blocks);
 
