@@ -273,6 +273,8 @@ static const void *field_kernel()
     return reinterpret_cast<const void *>(&k_batch_field<BLOCK, F32>);
 }
 
+// Nontemporal accesses and ascending order at every size; the single tubes' rule
+// (push_nontemporal, push_tile) has not been measured for batches.
 static const void *pick_push_kernel(pic_handle *h)
 {
     const bool f32 = h->tubes[0]->p.precision == PIC_FP32_BULK;

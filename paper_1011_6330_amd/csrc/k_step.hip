@@ -30,6 +30,8 @@
 
 namespace pcpic {
 
+// Nontemporal accesses in ascending order, as the separate pushes of the same sizes take
+// (push_nontemporal; a fused FP64 tube has 24 MiB of slots at most).
 constexpr int STEP_BLOCK = 128;
 constexpr int STEP_TILE_F64 = STEP_BLOCK * 2;
 constexpr int STEP_TILE_F32 = STEP_BLOCK * F32_PPT_HI;
