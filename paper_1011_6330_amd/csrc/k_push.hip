@@ -18,10 +18,10 @@
 // (exit, return, node-0 tally) are added by the lanes that have them.
 //
 // What bounds it: 4e7 particles move 1.28 GB per step, 192 us at the copy rate, and
-// take 209 (138 of vector instructions).  With the lapse (GR) the instructions do:
-// 440 per wave of 128 particles against 248, 6.1e6 particles 64.2 us with the general
-// reciprocals and 60.6 with those at hand, 38.6 of it issue, where their 195 MB stay
-// in the last-level cache.
+// take 201 (139 of vector instructions).  With the lapse (GR) the instructions do:
+// 459 per wave of 128 particles against 263, 6.1e6 particles 64.2 us with the general
+// reciprocals, 60.6 with those at hand and 59.1 in step_route.h's order, 39 of it issue,
+// where their 195 MB stay in the last-level cache.
 #include <math.h>
 
 #include "pcpic_internal.h"
