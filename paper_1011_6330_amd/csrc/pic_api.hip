@@ -384,14 +384,18 @@ int64_t host_jumps(int64_t n, int wave, F cell)
 {
     const int64_t stride = jump_stride(n);
     int64_t sum = 0;
-    for (int64_t g = 0; g < n; g += 256 * stride)
-        for (int64_t w = g; w < n && w < g + 256; w += wave) {
-            const int64_t e = w + wave < n ? w + wave : n;
-            int lo = INT_MAX;
-            for (int64_t i = w; i < e; ++i) lo = cell(i) >= 0 && cell(i) < lo ? cell(i) : lo;
-            for (int64_t i = w + 1; i < e; ++i)
-                sum += cell(i) >= 0 && cell(i) - lo > 62 && (cell(i) >> 3) != (cell(i - 1) >> 3);
+    int c[256];
+    for (int64_t g = 0; g < n; g += 256 * stride) {
+        const int m = (int)(n - g < 256 ? n - g : 256);
+        for (int i = 0; i < m; ++i) c[i] = cell(g + i);
+        for (int w = 0; w < m; w += wave) {
+            const int e = w + wave < m ? w + wave : m;
+            int lo = INT_MAX, jumps = 0;
+            for (int i = w; i < e; ++i) lo = c[i] >= 0 && c[i] < lo ? c[i] : lo;
+            for (int i = w + 1; i < e; ++i) jumps += c[i] >= 0 && c[i] - lo > 62 && (c[i] >> 3) != (c[i - 1] >> 3);
+            sum += jumps;
         }
+    }
     return sum * stride;
 }
 
@@ -1374,8 +1378,7 @@ pic_status pic_load(pic_handle *h, const void *buf, size_t bytes)
     }
     HIP_OK(hipMemcpyAsync(w.ctr, &ctr, sizeof ctr, hipMemcpyHostToDevice, h->stream));
     HIP_OK(launch_kick(h));
-    HIP_OK(hipStreamSynchronize(h->stream));
-    h->seen = hd.n_lo + hd.n_hi;
+    // counted while the copies are on their way
     auto cell32 = [&](size_t at) {
         return [&in, at](int64_t i) {
             int c;
@@ -1386,10 +1389,13 @@ pic_status pic_load(pic_handle *h, const void *buf, size_t bytes)
     auto cell64 = [&](int64_t i) {
         double x;
         memcpy(&x, in + L.p[0] + 8 * (size_t)i, 8);
-        return x >= 0.0 ? (int)x : -1;
+        return x >= 0.0 && x < (double)N ? (int)x : -1;
     };
-    h->jumps = f32 ? host_jumps(hd.n_lo, 256, cell32(L.p[0])) + host_jumps(hd.n_hi, 256, cell32(L.p[3]))
-                   : host_jumps(hd.n_lo, 128, cell64);
+    const int64_t jumps = f32 ? host_jumps(hd.n_lo, 256, cell32(L.p[0])) + host_jumps(hd.n_hi, 256, cell32(L.p[3]))
+                              : host_jumps(hd.n_lo, 128, cell64);
+    HIP_OK(hipStreamSynchronize(h->stream));
+    h->seen = hd.n_lo + hd.n_hi;
+    h->jumps = jumps;
     h->step = hd.step;
     return PIC_OK;
 }
